@@ -133,7 +133,16 @@ typedef struct gp_grid_params {
 
 typedef struct gp_grid gp_grid;
 
-/* Kernel configuration chosen by gp_autotune or set by hand (0 = library default). */
+/* Queries run on one of two paths, with the same results.  A grid carries a locator, a
+ * per-point index built with it (subcells with only the edges or segments that can decide
+ * a point there), unless its size, its cells against its coordinates (P2P: 2^28 and more
+ * cell sizes from the origin) or the device's memory forbid one; queries use it while the
+ * grid is at the library default.  An explicit gp_tuning, and every grid without a
+ * locator, runs the tiled refinement: points sorted by cell, every candidate test of a
+ * cell's points performed by a work item. */
+
+/* Configuration of the tiled refinement chosen by gp_autotune or set by hand (0 = library
+ * default). */
 typedef struct gp_tuning {
     int32_t points_per_lane; /* 1, 2 or 4: a work item holds up to 64*ppl points */
     int32_t edge_chunk;      /* edges staged in LDS per round: 64..512, multiple of 64
@@ -162,13 +171,15 @@ typedef struct gp_tuning {
 typedef struct gp_stats {
     int64_t n_points;     /* points in the call */
     int64_t n_paired;     /* points in a cell with >= 1 candidate */
-    int64_t n_items;      /* refinement work items (cell, point chunk) */
-    uint64_t tests;       /* point-edge tests performed: sum over cells npts * sum nedges
-                             over the candidates refined (all of them unless the grid
-                             was built with pip_cell_classes) */
-    int64_t n_rechecked;  /* GP_MIXED: points recomputed in FP64 */
-    float ms_pairing;     /* hash + sort + gather + item list */
-    float ms_refine;      /* refinement kernel */
+    int64_t n_items;      /* refinement work items: (cell, point chunk), or wavefronts of
+                             points on the locator */
+    uint64_t tests;       /* point-edge tests of the pairing: sum over cells npts * sum
+                             nedges over the candidates refined (all of them unless the
+                             grid was built with pip_cell_classes).  The tiled refinement
+                             performs each; the locator's index settles most of them */
+    int64_t n_rechecked;  /* GP_MIXED: points recomputed in FP64 (tiled refinement) */
+    float ms_pairing;     /* hash + sort + gather + item list (tiled refinement) */
+    float ms_refine;      /* refinement kernel, or the locator's query */
     float ms_recheck;     /* FP64 recheck kernel */
     float ms_total;
     uint64_t tests_avoided; /* candidate tests skipped by the cell classes (else 0) */
@@ -236,13 +247,15 @@ gp_status gp_query_noalloc(const gp_grid *grid, gp_kind kind, int64_t n, const d
                            const double *py, int32_t *out_id, double *out_dist,
                            gp_precision prec, void *hip_stream);
 
-/* Kernel configuration of a grid for one precision form.  gp_set_tuning with a NULL
- * tuning restores the library default. */
+/* Kernel configuration of a grid for one precision form.  gp_set_tuning selects the tiled
+ * refinement with that configuration; with a NULL tuning it restores the library default
+ * (the locator, where the grid has one). */
 gp_status gp_set_tuning(gp_grid *grid, gp_precision prec, const gp_tuning *tuning);
 gp_status gp_get_tuning(const gp_grid *grid, gp_precision prec, gp_tuning *tuning);
 
 /* Autotuner: times every configuration of a built-in search space on the given
- * (device) sample points, keeps the fastest, stores it in the grid and returns it.
+ * (device) sample points, keeps the fastest, stores it in the grid and returns it; queries
+ * stay on the grid's locator where that is at least as fast (*best_ms is the faster time).
  * Results never depend on the configuration.  The winner is cached in the process by
  * (operation, precision, GPU architecture, the grid's build-time options, workload class:
  * the octaves of the sample size, of the tests per paired point and of the paired points

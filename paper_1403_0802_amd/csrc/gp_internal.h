@@ -87,6 +87,11 @@ constexpr int64_t kPersistentMinPoints = int64_t(1) << 22;
 // 1M points with 6 per cell 0.55 against 0.59 ms, 1M with 25 per cell 2.28 against 2.70).
 constexpr int64_t kFourPerLaneMinPointsPerCell = 256;
 
+// Locator, PIP: a cell (first subcell, log2 subcells per side), or (answer, 0xff) when it is
+// not divided.
+struct LocCell {
+  uint32_t base, m;
+};
 struct Grid {
   gp_kind kind;
   int device;
@@ -121,9 +126,32 @@ struct Grid {
   int64_t *d_prec_off;
   int2 *d_pcnt;
   int64_t nprec;
+  LocCell *d_loc_cell;     // the locator (gp_locate.hip), null when the grid has none
+  int32_t *d_loc_sub;     // PIP
+  double4 *d_loc_slot;
+  int64_t loc_bytes;
   gp_tuning tune[2];
   bool tune_explicit[2];  // tune[prec] was set by gp_set_tuning or gp_autotune
   int num_cu;
+};
+
+// What the locator's queries read; a cell's subcells are numbered row by row.
+struct LocArgs {
+  double x0, y0, cs;
+  int32_t nx, ny;
+  const LocCell *cell;      // PIP: [ncells]
+  const int32_t *sub;       //   answer (>= -1) or -(first slot + 2)
+  const double4 *slot;      //   lists: per polygon a header and its elements
+};
+
+// What the build needs beside the grid: the (cell, feature) pairs' cells, the rings and the
+// vertices' y (PIP), and the largest coordinate magnitude of the vertices and the extent.
+struct LocBuild {
+  const uint32_t *pair_cell;
+  const int32_t *ring_off;
+  int32_t n_rings;
+  const double *vy;
+  double max_coord;
 };
 
 // Workspace layout for n points.
@@ -140,7 +168,8 @@ struct Workspace {
   uint32_t *vp_list;     // P2P: the vertex-parallel items (max_items)
   uint32_t *rq;
   uint32_t *counters;    // [16]: 0 item counter, 1 rq count, 2 n_items(copy), ...
-  unsigned long long *tests;  // [1]
+  unsigned long long *tests;  // [3]: tests, tests over all candidates, points paired
+                              // (the last by the locator's queries)
   size_t bytes;
 };
 
@@ -216,6 +245,19 @@ hipError_t launch_classify_pairs(const uint32_t *pair_cell, const int32_t *cand_
                                  int32_t npairs, const int32_t *eoff, const double4 *edge64,
                                  double x0, double y0, double cs, int32_t nx, double margin,
                                  uint8_t *cand_class, hipStream_t s);
+
+// locator (gp_locate.hip).  build_locator leaves the grid without one (and returns
+// hipSuccess) where its limits or the device's memory do not allow it.
+hipError_t build_locator(Grid &g, const LocBuild &b, hipStream_t s);
+LocArgs locator_args(const Grid &g);
+bool uses_locator(const Grid &g, gp_precision prec);  // gp_api.cpp
+// counts (or null): three counters the query zeroes for launch_locate_count, which adds
+// the candidate tests of the points' cells, those over `all` (or null) and the points paired.
+hipError_t launch_locate_pip(const LocArgs &a, const double *px, const double *py, int64_t n,
+                             int32_t *out_id, unsigned long long *counts, hipStream_t s);
+hipError_t launch_locate_count(const LocArgs &a, const double *px, const double *py, int64_t n,
+                               const int32_t *cand_off, const int64_t *cell_tests,
+                               const int64_t *all, unsigned long long *counts, hipStream_t s);
 
 // query pipeline
 hipError_t launch_hash(const double *px, const double *py, int64_t n, double x0, double y0,

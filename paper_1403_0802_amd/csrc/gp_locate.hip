@@ -1,0 +1,710 @@
+// Locator: the grid's exact per-point index, and the queries that read it.
+//
+// The paper's refinement tests every point of a cell against every edge of the cell's
+// candidates (Sec. III.B-C).  For a resident feature set most of those tests have the
+// same outcome for every point of the cell, or of a small part of it, so the grid build
+// settles them once: each cell is cut into k x k subcells (k a power of two, per cell),
+// and a subcell keeps only what can still differ between its points.
+//
+//   PIP   per candidate polygon, in id order, the parity of everything that is constant
+//         over the subcell, the edges whose crossing predicate is not, and the vertices
+//         where a chain of edges right of the subcell begins or ends inside its y band.
+//         Polygons with nothing left are either skipped or end the list (the subcell lies
+//         inside them).  Most subcells have a single answer and no list.
+//
+// A query is one kernel: a point per lane finds its subcell and evaluates the few entries
+// left with the FP64 predicates in the definition's operation order, so ids
+// are those of the definition, whatever the precision form.  No sort, no work items and no
+// scattered result stores: the kernel reads 16 bytes and writes 4 per point in the
+// caller's order, and is bound by the gathers of the index.
+//
+// Every bound of the build is conservative: boxes are padded by more than the rounding of
+// a point's cell and subcell, thresholds by more than the rounding of the FP64 predicates,
+// and comparisons keep an entry when a bound is NaN.
+#include <hip/hip_runtime.h>
+#include <math.h>
+#include <stdint.h>
+
+#include <algorithm>
+
+#include "gp_internal.h"
+
+namespace gp {
+
+#define GP_WAVE 64
+
+namespace {
+
+__device__ __forceinline__ uint64_t ballot(bool c) { return __builtin_amdgcn_ballot_w64(c); }
+__device__ __forceinline__ uint32_t lane_id() { return __lane_id(); }
+__device__ __forceinline__ uint64_t lanemask_lt() { return (1ull << lane_id()) - 1ull; }
+__device__ __forceinline__ int32_t uniform(int32_t v) { return __builtin_amdgcn_readfirstlane(v); }
+
+__device__ __forceinline__ void wave_lds_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+unsigned blocks_for(int64_t n, int64_t per, int64_t cap) {
+  return (unsigned)std::max<int64_t>(1, std::min<int64_t>((n + per - 1) / per, cap));
+}
+
+// ------------------------------------------------------------------------- PIP build
+
+// x of the stand-ins for chains of edges right of a subcell: far right of any point (the
+// build refuses coordinates of 1e150 and more), so such an edge's crossing is its straddle
+// lo.y <= p.y < hi.y alone: (p.x - X) * h < 0 * (p.y - lo.y) holds for every h > 0,
+// infinity included.
+constexpr double kFarX = 1e300;
+
+enum { LOC_NEVER = 0, LOC_RIGHT = 1, LOC_GUARD = 2 };
+
+struct Box {
+  double x0, y0, x1, y1;
+};
+
+// What edge e = (lo.x, lo.y, hi.x, hi.y) does for the points of box b: NEVER crosses;
+// RIGHT: the x part of the predicate holds for every point, so the crossing is the
+// straddle of p.y; GUARD: anything else.  The x part, (p.x - lo.x) h < w (p.y - lo.y), is
+// the sign of a function linear in p, so its extremes over the box are at the corners; tol
+// is over 50 times the rounding of the operations that evaluate it, here and at any point
+// of the box (and never 0, so a sign lost to underflow is GUARD).
+__device__ __forceinline__ int loc_class(const double4 e, const Box &b) {
+  if (e.w <= b.y0 || e.y > b.y1) return LOC_NEVER;
+  if (e.x >= 0.5 * kFarX) return LOC_RIGHT;
+  if (e.y == e.w) return fmin(e.x, e.z) > b.x1 ? LOC_RIGHT : LOC_NEVER;
+  const double h = e.w - e.y, w = e.z - e.x;
+  const double ax = (b.x0 - e.x) * h, bx = (b.x1 - e.x) * h;
+  const double ay = w * (b.y0 - e.y), by = w * (b.y1 - e.y);
+  const double lo = ax - fmax(ay, by), hi = bx - fmin(ay, by);
+  const double tol = 0x1p-44 * (fmax(fabs(ax), fabs(bx)) + fmax(fabs(ay), fabs(by))) + 0x1p-900;
+  if (hi < -tol) return LOC_RIGHT;
+  if (lo > tol) return LOC_NEVER;
+  return LOC_GUARD;
+}
+
+// Ring predecessor of every vertex (edge v joins vertex v and its ring successor).
+__global__ void k_loc_ring_prev(const int32_t *rvo, int32_t nr, int32_t *prev) {
+  for (int32_t r = blockIdx.x; r < nr; r += gridDim.x) {
+    const int32_t v0 = rvo[r], v1 = rvo[r + 1];
+    for (int32_t v = v0 + (int32_t)threadIdx.x; v < v1; v += blockDim.x)
+      prev[v] = v == v0 ? v1 - 1 : v - 1;
+  }
+}
+
+__device__ __forceinline__ Box cell_box(uint32_t cell, int32_t nx, double x0, double y0,
+                                        double cs, double pad) {
+  const double bx = x0 + (double)(cell % (uint32_t)nx) * cs;
+  const double by = y0 + (double)(cell / (uint32_t)nx) * cs;
+  return Box{bx - pad, by - pad, bx + cs + pad, by + cs + pad};
+}
+
+// Elements of every (cell, candidate polygon) pair, one wave per pair, lanes over the
+// polygon's vertices in ring order: the guarded edges, and each vertex in the cell's y band
+// with exactly one RIGHT edge.  The straddle of an edge (a, b) is [a.y <= y] xor [b.y <= y],
+// so over a chain of RIGHT edges the inner vertices cancel and its two ends remain; a
+// vertex v is kept as the far edge (v.y, +inf), whose straddle is [v.y <= y].  Ends below
+// the band are 1 for every point and go into the pair's parity.
+template <bool EMIT>
+__global__ __launch_bounds__(256) void k_loc_pip_pairs(
+    const uint32_t *pair_cell, const int32_t *cand_id, int32_t npairs, const int32_t *eoff,
+    const double4 *edge64, const double *vy, const int32_t *prev, double x0, double y0,
+    double cs, int32_t nx, double pad, uint32_t *cnt, uint8_t *par, double4 *elem) {
+  const uint64_t lt = lanemask_lt();
+  const int32_t nw = (int32_t)(gridDim.x * (blockDim.x / GP_WAVE));
+  for (int32_t k = uniform((int32_t)(blockIdx.x * (blockDim.x / GP_WAVE) + threadIdx.x / GP_WAVE));
+       k < npairs; k += nw) {
+    const Box b = cell_box(pair_cell[k], nx, x0, y0, cs, pad);
+    const int32_t f = cand_id[k], e1 = eoff[f + 1];
+    uint32_t n = EMIT ? cnt[k] : 0u;  // EMIT: cnt holds the pairs' first elements
+    uint32_t odd = 0;
+    for (int32_t base = eoff[f]; base < e1; base += GP_WAVE) {
+      const int32_t v = base + (int32_t)lane_id();
+      bool guard = false, end = false, below = false;
+      double4 e;
+      double y = 0.0;
+      if (v < e1) {
+        e = edge64[v];
+        y = vy[v];
+        const int c = loc_class(e, b), cp = loc_class(edge64[prev[v]], b);
+        guard = c == LOC_GUARD;
+        const bool brk = (c == LOC_RIGHT) != (cp == LOC_RIGHT);
+        below = brk && y <= b.y0;
+        end = brk && y > b.y0 && y <= b.y1;
+      }
+      const uint64_t mg = ballot(guard), me = ballot(end);
+      odd ^= (uint32_t)__popcll(ballot(below)) & 1u;
+      if constexpr (EMIT) {
+        uint32_t at = n + (uint32_t)(__popcll(mg & lt) + __popcll(me & lt));
+        if (end) elem[at++] = make_double4(kFarX, y, kFarX, INFINITY);
+        if (guard) elem[at] = e;
+      }
+      n += (uint32_t)(__popcll(mg) + __popcll(me));
+    }
+    if (!EMIT && lane_id() == 0) {
+      cnt[k] = n;
+      par[k] = (uint8_t)odd;
+    }
+  }
+}
+
+// Elements of every cell up to the first polygon that contains the whole cell, and the
+// cell's answer when there are none.  eoffs[k] are the pairs' first elements.  shape
+// [c] = log2 k, or LOC_CONST; cost[0] += subcells, cost[1] += subcells * elements,
+// cost[2] += groups of the list builder.
+constexpr uint32_t LOC_CONST = 0xffu;
+
+// A wave of the list builders takes a group of subcells: an 8 x 8 block, or the whole of a
+// cell with fewer.
+__device__ __forceinline__ uint32_t group_count(uint32_t m) {
+  return m > 3 ? 1u << (2 * (m - 3)) : 1u;
+}
+
+// log2 of the subdivision for a cell with E elements: about E / 4 subcells along a side, so
+// that a boundary crossing the cell leaves a few elements in the subcells it meets.
+__device__ __forceinline__ uint32_t pip_shape(uint32_t E, uint32_t cap) {
+  const uint32_t m = E <= 4 ? 2u : E <= 24 ? 3u : E <= 96 ? 4u : E <= 384 ? 5u : 6u;
+  return m < cap ? m : cap;
+}
+
+__global__ __launch_bounds__(256) void k_loc_pip_cells(const int32_t *cand_off,
+                                                       const int32_t *cand_id, int32_t ncells,
+                                                       const uint32_t *eoffs, const uint8_t *par,
+                                                       uint32_t cap, uint32_t *nsub,
+                                                       LocCell *cell,
+                                                       unsigned long long *cost) {
+  unsigned long long s0 = 0, s1 = 0, s2 = 0;
+  for (int32_t c = blockIdx.x * blockDim.x + threadIdx.x; c <= ncells;
+       c += gridDim.x * blockDim.x) {
+    uint32_t E = 0;
+    int32_t ans = -1;
+    if (c < ncells) {
+      const int32_t k1 = cand_off[c + 1];
+      for (int32_t k = cand_off[c]; k < k1; ++k) {
+        const uint32_t n = eoffs[k + 1] - eoffs[k];
+        E += n;
+        if (n == 0 && par[k]) {
+          ans = cand_id[k];
+          break;
+        }
+      }
+      const uint32_t m = pip_shape(E, cap);
+      const uint32_t q = E ? 1u << (2 * m) : 0u;
+      nsub[c] = q;
+      cell[c] = LocCell{(uint32_t)ans, E ? m : LOC_CONST};
+      s0 += q;
+      s1 += (unsigned long long)q * E;
+      s2 += E ? group_count(m) : 0u;
+    } else {
+      nsub[c] = 0;
+    }
+  }
+  for (int off = 32; off > 0; off >>= 1) {
+    s0 += __shfl_xor(s0, off, GP_WAVE);
+    s1 += __shfl_xor(s1, off, GP_WAVE);
+    s2 += __shfl_xor(s2, off, GP_WAVE);
+  }
+  if (lane_id() == 0 && s1) {
+    atomicAdd(cost, s0);
+    atomicAdd(cost + 1, s1);
+    atomicAdd(cost + 2, s2);
+  }
+}
+
+// Subcell base of every divided cell, from the scan of nsub.
+template <class Cell>
+__global__ void k_loc_cell_base(const uint32_t *base, int32_t ncells, Cell *cell) {
+  for (int32_t c = blockIdx.x * blockDim.x + threadIdx.x; c < ncells; c += gridDim.x * blockDim.x)
+    if (cell[c].m != LOC_CONST) cell[c].base = base[c];
+}
+
+// The groups (cell, block), in no particular order.  One atomic per wave.
+template <class Cell>
+__global__ __launch_bounds__(256) void k_loc_groups(const Cell *cell, int32_t ncells,
+                                                    uint32_t *n, int2 *group) {
+  for (int32_t c0 = blockIdx.x * blockDim.x; c0 < ncells; c0 += gridDim.x * blockDim.x) {
+    const int32_t c = c0 + (int32_t)threadIdx.x;
+    const uint32_t m = c < ncells ? cell[c].m : LOC_CONST;
+    const uint32_t q = m == LOC_CONST ? 0u : group_count(m);
+    uint32_t inc = q;
+#pragma unroll
+    for (int off = 1; off < GP_WAVE; off <<= 1) {
+      const uint32_t u = __shfl_up(inc, off, GP_WAVE);
+      if (lane_id() >= (uint32_t)off) inc += u;
+    }
+    uint32_t o = 0;
+    if (lane_id() == GP_WAVE - 1 && inc) o = atomicAdd(n, inc);
+    o = (uint32_t)__builtin_amdgcn_readlane((int32_t)o, GP_WAVE - 1) + inc - q;
+    for (uint32_t k = 0; k < q; ++k) group[o + k] = make_int2(c, (int32_t)k);
+  }
+}
+
+// The lane's subcell of a group: column, row and whether it exists; the group's columns and
+// rows start at gx, gy and it is gw subcells wide.
+struct GroupLane {
+  int32_t gx, gy, gw, sx, sy;
+  bool act;
+};
+__device__ __forceinline__ GroupLane group_lane(uint32_t m, int32_t block) {
+  GroupLane g;
+  g.gw = m > 3 ? 8 : 1 << m;
+  const int32_t bw = m > 3 ? 1 << (m - 3) : 1;  // blocks along a side
+  g.gx = block % bw * 8;
+  g.gy = block / bw * 8;
+  const int32_t l = (int32_t)lane_id();
+  g.act = l < g.gw * g.gw;
+  g.sx = g.gx + l % g.gw;
+  g.sy = g.gy + (l / g.gw) % g.gw;  // idle lanes repeat the active ones' places
+  return g;
+}
+
+// A subcell's list: per polygon a header slot (int4 x 2: id, elements << 1 | parity, 1 if
+// another polygon follows, the id that ends the list or -1) and its elements.
+struct alignas(32) LocHead {
+  int32_t f, npar, more, last, pad[4];
+};
+static_assert(sizeof(LocHead) == sizeof(double4), "a header takes one slot");
+
+// Lists of the subcells, one wave per group, lanes over its subcells.  The cell's elements
+// pass 64 at a time, a lane each, and those that cannot cross anywhere in the group are
+// dropped; the rest are broadcast through LDS.  Elements that are RIGHT for a subcell are
+// merged along their chains: a run is the far edge {ra, rb} standing for the edges merged
+// so far, and an edge that shares an end with it (by y, which is all its straddle depends
+// on) extends it.  Ends outside the subcell's band count as -inf or +inf, so a chain that
+// leaves the band and returns merges too, and one that passes through it becomes a constant.
+// EMIT = false: slots per subcell in cnt (0: a single answer).  EMIT: cnt holds the first
+// slots; writes the lists and sub[s] = answer (>= -1) or -(first slot + 2).
+template <bool EMIT>
+__global__ __launch_bounds__(256) void k_loc_pip_sub(
+    const int32_t *cand_off, const int32_t *cand_id, const int2 *group, uint32_t ngroups,
+    const uint32_t *eoffs, const uint8_t *par, const double4 *elem, const LocCell *cell,
+    double x0, double y0, double cs, int32_t nx, double pad, uint32_t *cnt, double4 *slot,
+    int32_t *sub) {
+  __shared__ double4 se[256 / GP_WAVE][GP_WAVE];
+  const int wave = (int)(threadIdx.x / GP_WAVE);
+  const uint32_t w = (uint32_t)uniform((int32_t)(blockIdx.x * (blockDim.x / GP_WAVE)) + wave);
+  if (w >= ngroups) return;
+  const int2 gr = group[w];
+  const int32_t c = uniform(gr.x);
+  const LocCell ce = cell[c];
+  const GroupLane g = group_lane(ce.m, uniform(gr.y));
+  const double a = cs / (double)(1u << ce.m);  // exact: a power of two
+  const double ox = x0 + (double)(c % nx) * cs, oy = y0 + (double)(c / nx) * cs;
+  const double gx = ox + (double)g.gx * a, gy = oy + (double)g.gy * a, gs = (double)g.gw * a;
+  const Box gb{gx - pad, gy - pad, gx + gs + pad, gy + gs + pad};
+  const double sx = ox + (double)g.sx * a, sy = oy + (double)g.sy * a;
+  const Box b{sx - pad, sy - pad, sx + a + pad, sy + a + pad};
+  const uint32_t at = ce.base + ((uint32_t)g.sy << ce.m) + (uint32_t)g.sx;
+  const uint32_t first = EMIT && g.act ? cnt[at] : 0u;
+  uint32_t n = 0;     // slots so far
+  uint32_t hpos = 0;  // open header (EMIT)
+  LocHead hd{-1, 0, 0, -1, {0, 0, 0, 0}};
+  bool open = false, done = !g.act;
+  int32_t last = -1;
+  const int32_t k1 = cand_off[c + 1];
+  for (int32_t k = cand_off[c]; k < k1; ++k) {
+    if (ballot(!done) == 0) break;
+    const uint32_t e0 = (uint32_t)uniform((int32_t)eoffs[k]);
+    const uint32_t e1 = (uint32_t)uniform((int32_t)eoffs[k + 1]);
+    uint32_t p = par[k];
+    uint32_t m = 0;  // this polygon's elements here
+    double ra = 0.0, rb = 0.0;
+    const uint32_t hslot = n;
+    auto put = [&](const double4 e) {
+      if (EMIT && !done) slot[first + hslot + 1 + m] = e;
+      ++m;
+    };
+    auto flush = [&]() {
+      if (ra != rb) {
+        const double lo = fmin(ra, rb), hi = fmax(ra, rb);
+        if (lo == -INFINITY) {
+          p ^= 1u;
+          if (hi != INFINITY) put(make_double4(kFarX, hi, kFarX, INFINITY));
+        } else {
+          put(make_double4(kFarX, lo, kFarX, hi));
+        }
+      }
+      ra = rb = 0.0;
+    };
+    for (uint32_t j0 = e0; j0 < e1; j0 += GP_WAVE) {
+      const uint32_t j = j0 + lane_id();
+      double4 mine;
+      bool use = false;
+      if (j < e1) {
+        mine = elem[j];
+        use = loc_class(mine, gb) != LOC_NEVER;
+      }
+      const uint64_t mk = ballot(use);
+      wave_lds_sync();
+      if (use) se[wave][__popcll(mk & lanemask_lt())] = mine;
+      wave_lds_sync();
+      const int nu = (int)__popcll(mk);
+      for (int q = 0; q < nu; ++q) {
+        const double4 e = se[wave][q];
+        const int cl = loc_class(e, b);
+        if (cl == LOC_GUARD) {
+          put(e);
+        } else if (cl == LOC_RIGHT) {
+          const double l = e.y <= b.y0 ? -INFINITY : e.y;
+          const double h = e.w > b.y1 ? INFINITY : e.w;
+          if (ra == rb) { ra = l; rb = h; }
+          else if (l == rb) rb = h;
+          else if (h == rb) rb = l;
+          else if (l == ra) ra = h;
+          else if (h == ra) ra = l;
+          else { flush(); ra = l; rb = h; }
+        }
+      }
+    }
+    flush();
+    if (done) continue;
+    const int32_t f = cand_id[k];
+    if (m == 0) {
+      if (p) {
+        last = f;
+        done = true;
+      }
+      continue;
+    }
+    if (EMIT) {
+      if (open) {
+        hd.more = 1;
+        *(LocHead *)&slot[first + hpos] = hd;
+      }
+      hd.f = f;
+      hd.npar = (int32_t)(m << 1 | p);
+      hpos = hslot;
+    }
+    open = true;
+    n += 1 + m;
+  }
+  if (!g.act) return;
+  if (EMIT) {
+    if (open) {
+      hd.more = 0;
+      hd.last = last;
+      *(LocHead *)&slot[first + hpos] = hd;
+    }
+    sub[at] = open ? -(int32_t)(first + 2u) : last;
+  } else {
+    cnt[at] = n;
+  }
+}
+
+// ------------------------------------------------------------------------- queries
+
+// The point's cell, as the pairing computes it (-1 when unpaired), and its place in the
+// cell in units of a cell: fx - floor(fx) and its product with a power of two are exact.
+__device__ __forceinline__ int32_t locate_cell(const LocArgs &a, double x, double y, double &ux,
+                                               double &uy) {
+  const double fx = (x - a.x0) / a.cs, fy = (y - a.y0) / a.cs;
+  const double cx = floor(fx), cy = floor(fy);
+  const bool ok = cx >= 0.0 && cx < (double)a.nx && cy >= 0.0 && cy < (double)a.ny;
+  ux = fx - cx;
+  uy = fy - cy;
+  return ok ? (int32_t)cy * a.nx + (int32_t)cx : -1;
+}
+
+__device__ __forceinline__ uint32_t subcell(uint32_t base, uint32_t m, double ux, double uy) {
+  const double k = (double)(1u << m);
+  return base + ((uint32_t)(uy * k) << m) + (uint32_t)(ux * k);
+}
+
+// Zeroes the counters that k_locate_count adds to next on the same stream.
+__device__ __forceinline__ void reset_counts(unsigned long long *counts) {
+  if (counts && blockIdx.x == 0 && threadIdx.x < 3) counts[threadIdx.x] = 0;
+}
+
+// One point per lane.  Bound by the gathers of the index (a cell, then for a divided cell its
+// subcell, then for the few subcells with a list its slots); a point needs no sorting for
+// them, because a whole map's directory stays in the caches.  Region map of 1.5M vertices:
+// 50M points 6.7 -> 1.02 ms against the tiled refinement, 1M points on a plain grid
+// 2.3 -> 0.032 ms, 1,500 points 0.30 -> 0.008 ms.
+__global__ __launch_bounds__(256) void k_locate_pip(LocArgs a, const double *px,
+                                                    const double *py, int64_t n,
+                                                    int32_t *out_id,
+                                                    unsigned long long *counts) {
+  reset_counts(counts);
+  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
+       i += (int64_t)gridDim.x * blockDim.x) {
+    const double x = px[i], y = py[i];
+    double ux, uy;
+    const int32_t c = locate_cell(a, x, y, ux, uy);
+    int32_t ans = -1;
+    if (c >= 0) {
+      const LocCell ce = a.cell[c];
+      ans = (int32_t)ce.base;
+      if (ce.m != LOC_CONST) {
+        ans = a.sub[subcell(ce.base, ce.m, ux, uy)];
+        if (ans < -1) {
+          const double4 *s = a.slot + (uint32_t)(-(ans + 2));
+          for (;;) {
+            const int4 hd = *(const int4 *)s;  // id, elements << 1 | parity, more, last
+            const int m = hd.y >> 1;
+            uint32_t odd = (uint32_t)hd.y & 1u;
+            for (int j = 1; j <= m; ++j) {
+              const double4 e = s[j];
+              const bool st = (e.y <= y) & (y < e.w);
+              const double lhs = (x - e.x) * (e.w - e.y), rhs = (e.z - e.x) * (y - e.y);
+              odd ^= (uint32_t)(st & (lhs < rhs));
+            }
+            ans = odd ? hd.x : hd.w;
+            if (odd || !hd.z) break;
+            s += m + 1;
+          }
+        }
+      }
+    }
+    out_id[i] = ans;
+  }
+}
+
+// The counters of a query: the candidate tests of its points' cells (counts[0]; counts[1]
+// over all candidates, when `all` is given) and its points in a cell with candidates
+// (counts[2]).
+__global__ __launch_bounds__(256) void k_locate_count(LocArgs a, const double *px,
+                                                      const double *py, int64_t n,
+                                                      const int32_t *cand_off,
+                                                      const int64_t *cell_tests,
+                                                      const int64_t *all,
+                                                      unsigned long long *counts) {
+  __shared__ unsigned long long sum[3][256 / GP_WAVE];
+  unsigned long long t = 0, ta = 0, np = 0;
+  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
+       i += (int64_t)gridDim.x * blockDim.x) {
+    double ux, uy;
+    const int32_t c = locate_cell(a, px[i], py[i], ux, uy);
+    if (c < 0 || cand_off[c + 1] == cand_off[c]) continue;
+    ++np;
+    t += (unsigned long long)cell_tests[c];
+    if (all) ta += (unsigned long long)all[c];
+  }
+  for (int off = 32; off > 0; off >>= 1) {
+    t += __shfl_xor(t, off, GP_WAVE);
+    ta += __shfl_xor(ta, off, GP_WAVE);
+    np += __shfl_xor(np, off, GP_WAVE);
+  }
+  if (lane_id() == 0) {
+    sum[0][threadIdx.x / GP_WAVE] = t;
+    sum[1][threadIdx.x / GP_WAVE] = ta;
+    sum[2][threadIdx.x / GP_WAVE] = np;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < 256 / GP_WAVE; ++w) {
+      t += sum[0][w];
+      ta += sum[1][w];
+      np += sum[2][w];
+    }
+    if (np) {
+      atomicAdd(counts, t);
+      if (all) atomicAdd(counts + 1, ta);
+      atomicAdd(counts + 2, np);
+    }
+  }
+}
+
+}  // namespace
+
+// ------------------------------------------------------------------------- launchers
+
+#define LAUNCH(k, g, b, ...)                                  \
+  do {                                                        \
+    hipLaunchKernelGGL(k, dim3(g), dim3(b), 0, s, __VA_ARGS__); \
+    return hipGetLastError();                                 \
+  } while (0)
+
+static hipError_t launch_loc_ring_prev(const int32_t *rvo, int32_t nr, int32_t *prev, hipStream_t s) {
+  if (nr <= 0) return hipSuccess;
+  LAUNCH(k_loc_ring_prev, blocks_for(nr, 1, 65536), 64, rvo, nr, prev);
+}
+
+static hipError_t launch_loc_pip_pairs(const Grid &g, const uint32_t *pair_cell, const double *vy,
+                                const int32_t *prev, double pad, uint32_t *cnt, uint8_t *par,
+                                double4 *elem, hipStream_t s) {
+  const unsigned b = blocks_for(g.npairs, 4, 65536);
+  if (elem)
+    LAUNCH(k_loc_pip_pairs<true>, b, 256, pair_cell, g.d_cand_id, g.npairs, g.d_eoff,
+           g.d_edge64, vy, prev, g.x0, g.y0, g.cs, g.nx, pad, cnt, par, elem);
+  LAUNCH(k_loc_pip_pairs<false>, b, 256, pair_cell, g.d_cand_id, g.npairs, g.d_eoff, g.d_edge64,
+         vy, prev, g.x0, g.y0, g.cs, g.nx, pad, cnt, par, elem);
+}
+
+static hipError_t launch_loc_pip_cells(const Grid &g, const uint32_t *eoffs, const uint8_t *par,
+                                       uint32_t cap, uint32_t *nsub, LocCell *cell,
+                                       unsigned long long *cost, hipStream_t s) {
+  LAUNCH(k_loc_pip_cells, blocks_for((int64_t)g.ncells + 1, 256, 8192), 256, g.d_cand_off,
+         g.d_cand_id, g.ncells, eoffs, par, cap, nsub, cell, cost);
+}
+
+// Subcell bases of the cells from the scan of nsub, and their groups; *n is zeroed here.
+template <class Cell>
+static hipError_t launch_loc_groups(const uint32_t *base, int32_t ncells, Cell *cell,
+                                    uint32_t *n, int2 *group, hipStream_t s) {
+  const unsigned b = blocks_for(ncells, 256, 8192);
+  hipError_t e = launch_fill_u32(n, 0u, 1, s);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_loc_cell_base<Cell>, dim3(b), dim3(256), 0, s, base, ncells, cell);
+  e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  LAUNCH(k_loc_groups<Cell>, b, 256, cell, ncells, n, group);
+}
+
+static hipError_t launch_loc_pip_sub(const Grid &g, const int2 *group, uint32_t ngroups,
+                                     const uint32_t *eoffs, const uint8_t *par,
+                                     const double4 *elem, const LocCell *cell, double pad,
+                                     uint32_t *cnt, double4 *slot, int32_t *sub, hipStream_t s) {
+  const unsigned b = (ngroups + 3) / 4;
+  if (sub)
+    LAUNCH(k_loc_pip_sub<true>, b, 256, g.d_cand_off, g.d_cand_id, group, ngroups, eoffs, par,
+           elem, cell, g.x0, g.y0, g.cs, g.nx, pad, cnt, slot, sub);
+  LAUNCH(k_loc_pip_sub<false>, b, 256, g.d_cand_off, g.d_cand_id, group, ngroups, eoffs, par,
+         elem, cell, g.x0, g.y0, g.cs, g.nx, pad, cnt, slot, sub);
+}
+
+hipError_t launch_locate_pip(const LocArgs &a, const double *px, const double *py, int64_t n,
+                             int32_t *out_id, unsigned long long *counts, hipStream_t s) {
+  LAUNCH(k_locate_pip, blocks_for(n, 256, 1 << 24), 256, a, px, py, n, out_id, counts);
+}
+
+hipError_t launch_locate_count(const LocArgs &a, const double *px, const double *py, int64_t n,
+                               const int32_t *cand_off, const int64_t *cell_tests,
+                               const int64_t *all, unsigned long long *counts, hipStream_t s) {
+  LAUNCH(k_locate_count, blocks_for(n, 1024, 2048), 256, a, px, py, n, cand_off, cell_tests, all,
+         counts);
+}
+
+
+// ------------------------------------------------------------------------- build
+
+namespace {
+
+// Limits of the index: slots of 32 bytes, tests of the build, and entries per subcell beyond which the tiled refinement, which
+// reads a list once for 64 and more points, is the better reader of it.
+constexpr int64_t kMaxSlots = int64_t(1) << 27;     // 4 GiB
+constexpr int64_t kMaxElems = int64_t(1) << 26;     // 2 GiB while building
+constexpr int64_t kMaxSubcells = int64_t(1) << 27;  // 512 MiB
+constexpr int64_t kMaxCells = int64_t(1) << 26;
+constexpr int64_t kMaxBuildTests = int64_t(1) << 33;
+constexpr int64_t kMaxMeanEntries = 64;
+
+struct Buf {
+  void *p = nullptr;
+  ~Buf() { if (p) (void)hipFree(p); }
+  bool alloc(size_t bytes) {
+    if (hipMalloc(&p, bytes ? bytes : 16) == hipSuccess) return true;
+    (void)hipGetLastError();  // no memory for it: the grid does without
+    p = nullptr;
+    return false;
+  }
+  template <class T> T *as() const { return (T *)p; }
+  template <class T> T *take() { T *q = (T *)p; p = nullptr; return q; }
+};
+
+#define LOC_TRY(expr)                      \
+  do {                                     \
+    const hipError_t e_ = (expr);          \
+    if (e_ != hipSuccess) return e_;       \
+  } while (0)
+#define LOC_NEED(cond)                     \
+  do {                                     \
+    if (!(cond)) return hipSuccess;        \
+  } while (0)
+
+hipError_t read_back(void *dst, const void *src, size_t bytes, hipStream_t s) {
+  LOC_TRY(hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, s));
+  return hipStreamSynchronize(s);
+}
+
+// cnt[0 .. n) becomes its exclusive prefix sum with the total at cnt[n]; *total in 64 bits
+// (nothing is scanned when it passes `most`).
+hipError_t scan_counts(uint32_t *cnt, size_t n, int64_t most, Buf &sum, uint32_t *tmp,
+                       int64_t *total, hipStream_t s) {
+  unsigned long long t = 0;
+  LOC_TRY(launch_fill_u32(cnt + n, 0u, 1, s));
+  LOC_TRY(launch_sum_u32(cnt, n, sum.as<unsigned long long>(), s));
+  LOC_TRY(read_back(&t, sum.p, 8, s));
+  *total = t > (unsigned long long)INT64_MAX ? INT64_MAX : (int64_t)t;
+  if (*total > most) return hipSuccess;
+  return launch_exclusive_scan_u32(cnt, cnt, n + 1, tmp, s);
+}
+
+hipError_t build_pip(Grid &g, const LocBuild &b, double pad, hipStream_t s) {
+  const size_t np = (size_t)g.npairs, nc = (size_t)g.ncells;
+  Buf prev, cnt, par, elem, nsub, cell, sum, tmp, scnt, sub, slot, subtmp, group;
+  LOC_NEED(prev.alloc((size_t)g.nedges * 4) && cnt.alloc((np + 1) * 4) && par.alloc(np) &&
+           nsub.alloc((nc + 1) * 4) && cell.alloc(nc * sizeof(LocCell)) && sum.alloc(64) &&
+           tmp.alloc(scan_tmp_elems(std::max(np, nc) + 1) * 4));
+  int64_t total = 0;
+  LOC_TRY(launch_loc_ring_prev(b.ring_off, b.n_rings, prev.as<int32_t>(), s));
+  if (np)
+    LOC_TRY(launch_loc_pip_pairs(g, b.pair_cell, b.vy, prev.as<int32_t>(), pad,
+                                 cnt.as<uint32_t>(), par.as<uint8_t>(), nullptr, s));
+  LOC_TRY(scan_counts(cnt.as<uint32_t>(), np, kMaxElems, sum, tmp.as<uint32_t>(), &total, s));
+  LOC_NEED(total <= kMaxElems && elem.alloc((size_t)total * 32));
+  if (total)
+    LOC_TRY(launch_loc_pip_pairs(g, b.pair_cell, b.vy, prev.as<int32_t>(), pad,
+                                 cnt.as<uint32_t>(), par.as<uint8_t>(), elem.as<double4>(), s));
+  // the finest subdivision whose size and build stay within the limits
+  unsigned long long cost[3] = {0, 0, 0};
+  for (int cap = 6; cap >= 0; --cap) {
+    LOC_TRY(launch_fill_u32(sum.as<uint32_t>(), 0u, 6, s));
+    LOC_TRY(launch_loc_pip_cells(g, cnt.as<uint32_t>(), par.as<uint8_t>(), (uint32_t)cap,
+                                 nsub.as<uint32_t>(), cell.as<LocCell>(),
+                                 sum.as<unsigned long long>(), s));
+    LOC_TRY(read_back(cost, sum.p, 24, s));
+    if (cost[0] <= (unsigned long long)kMaxSubcells && cost[1] <= (unsigned long long)kMaxBuildTests)
+      break;
+    LOC_NEED(cap > 0);
+  }
+  const size_t ns = (size_t)cost[0];
+  LOC_TRY(launch_exclusive_scan_u32(nsub.as<uint32_t>(), nsub.as<uint32_t>(), nc + 1,
+                                    tmp.as<uint32_t>(), s));
+  const uint32_t ng = (uint32_t)cost[2];
+  LOC_NEED(group.alloc((size_t)ng * 8));
+  LOC_TRY(launch_loc_groups(nsub.as<uint32_t>(), g.ncells, cell.as<LocCell>(),
+                            sum.as<uint32_t>(), group.as<int2>(), s));
+  total = 0;
+  LOC_NEED(sub.alloc(ns * 4) && scnt.alloc((ns + 1) * 4) &&
+           subtmp.alloc(scan_tmp_elems(ns + 1) * 4));
+  if (ns) {
+    LOC_TRY(launch_loc_pip_sub(g, group.as<int2>(), ng, cnt.as<uint32_t>(), par.as<uint8_t>(),
+                               elem.as<double4>(), cell.as<LocCell>(), pad, scnt.as<uint32_t>(), nullptr, nullptr, s));
+    LOC_TRY(scan_counts(scnt.as<uint32_t>(), ns, kMaxSlots, sum, subtmp.as<uint32_t>(), &total, s));
+    LOC_NEED(total <= kMaxSlots && total <= kMaxMeanEntries * (int64_t)ns);
+    LOC_NEED(slot.alloc((size_t)total * 32));
+    LOC_TRY(launch_loc_pip_sub(g, group.as<int2>(), ng, cnt.as<uint32_t>(), par.as<uint8_t>(),
+                               elem.as<double4>(), cell.as<LocCell>(), pad, scnt.as<uint32_t>(), slot.as<double4>(),
+                               sub.as<int32_t>(), s));
+  }
+  LOC_TRY(hipStreamSynchronize(s));  // before the temporaries go
+  g.d_loc_cell = cell.take<LocCell>();
+  g.d_loc_sub = sub.take<int32_t>();
+  g.d_loc_slot = slot.take<double4>();
+  g.loc_bytes = (int64_t)(nc * sizeof(LocCell) + ns * 4) + total * 32;
+  return hipSuccess;
+}
+
+}  // namespace
+
+hipError_t build_locator(Grid &g, const LocBuild &b, hipStream_t s) {
+  if (g.ncells > kMaxCells || !(b.max_coord < 1e150) || !(g.cs > 1e-140)) return hipSuccess;
+  // pads: as the MBBs', and over 1000 times the rounding of a point's cell and subcell
+  const double pad = g.cs * 0x1p-20 + b.max_coord * 0x1p-40;
+  return build_pip(g, b, pad, s);
+}
+
+LocArgs locator_args(const Grid &g) {
+  LocArgs a;
+  a.x0 = g.x0;
+  a.y0 = g.y0;
+  a.cs = g.cs;
+  a.nx = g.nx;
+  a.ny = g.ny;
+  a.cell = g.d_loc_cell;
+  a.sub = g.d_loc_sub;
+  a.slot = g.d_loc_slot;
+  return a;
+}
+
+}  // namespace gp

@@ -48,7 +48,7 @@ gp_status set_error(gp_status code, const char *fmt, ...);
 gp_status run_query_tuned(const gp_grid *g, gp_kind kind, int64_t n, const double *px,
                           const double *py, int32_t *out_id, double *out_dist,
                           gp_precision prec, void *ws, size_t ws_bytes, hipStream_t s,
-                          gp_stats *stats, const gp_tuning *t);
+                          gp_stats *stats, const gp_tuning *t, bool count);
 }  // namespace gp
 
 using namespace gp;
@@ -278,12 +278,14 @@ static gp_status enqueue_chunk(gp_server *srv, Lane &ln, Request *r, Block *blk,
   // vertex-parallel (lanes over edges or segments) instead of leaving most lanes idle
   if (tn.vp_points < 0 && (double)b < 4.0 * (double)((const Grid *)g)->ncells)
     tn.vp_points = 4;
+  // a grid at the library default runs its chunks on the locator
+  const gp_tuning *tp = uses_locator(*(const Grid *)g, prec) ? nullptr : &tn;
   if (o.use_graphs) {
     if (!blk->graph) {
       hipGraph_t graph;
       SV_TRY(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
       gp_status rc = run_query_tuned(g, r->kind, b, blk->px, blk->py, blk->id, blk->dist, prec,
-                                     blk->ws, blk->ws_bytes, s, nullptr, &tn);
+                                     blk->ws, blk->ws_bytes, s, nullptr, tp, true);
       hipError_t ec = hipStreamEndCapture(s, &graph);
       if (rc) return rc;
       SV_TRY(ec);
@@ -298,7 +300,7 @@ static gp_status enqueue_chunk(gp_server *srv, Lane &ln, Request *r, Block *blk,
     srv->replays++;
   } else {
     gp_status rc = run_query_tuned(g, r->kind, m, blk->px, blk->py, blk->id, blk->dist, prec,
-                                   blk->ws, blk->ws_bytes, s, nullptr, &tn);
+                                   blk->ws, blk->ws_bytes, s, nullptr, tp, true);
     if (rc) return rc;
   }
   SV_TRY(hipMemcpyAsync(r->out_id + lo, blk->id, (size_t)m * 4, out_kind, s));
