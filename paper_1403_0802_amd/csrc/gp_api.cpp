@@ -469,7 +469,7 @@ extern "C" gp_status gp_build_grid(gp_kind kind, const gp_geometry *geom,
     lb.vy = d_y.as<double>();
     lb.max_coord = std::max({max_coord, std::fabs(x0), std::fabs(y0),
                              std::fabs(x0 + (double)nx * cs), std::fabs(y0 + (double)ny * cs)});
-    if (kind == GP_PIP) GP_TRY_HIP_G(build_locator(*g, lb, s));
+    GP_TRY_HIP_G(build_locator(*g, lb, s));
   }
   if (kind == GP_P2P && params->p2p_segment_filter && nedges > 0) {
     // (cell, segment) pairs: every segment's box, expanded by D and padded like the MBBs,
@@ -574,6 +574,10 @@ extern "C" void gp_grid_free(gp_grid *g) {
   (void)hipFree(g->d_loc_cell);
   (void)hipFree(g->d_loc_sub);
   (void)hipFree(g->d_loc_slot);
+  (void)hipFree(g->d_loc_soff);
+  (void)hipFree(g->d_loc_seg);
+  (void)hipFree(g->d_loc_scell);
+  (void)hipFree(g->d_loc_ent);
   delete g;
 }
 
@@ -704,7 +708,7 @@ static hipError_t pair_points(const Grid &g, int64_t n, const double *px, const 
 // Whether queries of the grid at its own tuning run on the locator: where the grid has
 // one and the caller has not asked for a configuration of the tiled refinement.
 bool uses_locator(const Grid &g, gp_precision prec) {
-  return g.d_loc_cell && !g.tune_explicit[prec];
+  return (g.d_loc_cell || g.d_loc_scell) && !g.tune_explicit[prec];
 }
 
 // The query on the locator; both precision forms, whose results are the same bits.
@@ -720,7 +724,8 @@ static gp_status run_locator(const gp_grid *g, int64_t n, const double *px, cons
     GP_TRY_HIP(hipEventRecord(ev[0], s));
   }
   unsigned long long *counts = count ? w.tests : nullptr;
-  GP_TRY_HIP(launch_locate_pip(a, px, py, n, out_id, counts, s));
+  if (g->kind == GP_PIP) GP_TRY_HIP(launch_locate_pip(a, px, py, n, out_id, counts, s));
+  else GP_TRY_HIP(launch_locate_p2p(a, px, py, n, out_id, out_dist, counts, s));
   if (stats) GP_TRY_HIP(hipEventRecord(ev[1], s));
   const bool segf = prec == GP_MIXED && g->d_cseg_off != nullptr;
   const int64_t *all = segf ? g->d_cell_edges : g->d_cell_edges_all;

@@ -92,6 +92,22 @@ constexpr int64_t kFourPerLaneMinPointsPerCell = 256;
 struct LocCell {
   uint32_t base, m;
 };
+// Locator, P2P: a cell (first subcell, log2 subcells per side or 0xff without segments, and
+// its reach), an entry of a subcell's list (endpoints a and b, x | y << 16 in steps of the
+// cell's frame, and the segment) and a segment by value with its polyline.
+struct alignas(16) LocSegCell {
+  uint32_t base, m;
+  double reach;
+};
+struct LocEntry {
+  uint32_t a, b;
+  int32_t seg;
+};
+struct alignas(64) LocSeg {
+  double4 e;
+  int32_t f;
+};
+
 struct Grid {
   gp_kind kind;
   int device;
@@ -129,6 +145,10 @@ struct Grid {
   LocCell *d_loc_cell;     // the locator (gp_locate.hip), null when the grid has none
   int32_t *d_loc_sub;     // PIP
   double4 *d_loc_slot;
+  uint32_t *d_loc_soff;   // P2P
+  LocSegCell *d_loc_scell;
+  LocEntry *d_loc_ent;
+  LocSeg *d_loc_seg;
   int64_t loc_bytes;
   gp_tuning tune[2];
   bool tune_explicit[2];  // tune[prec] was set by gp_set_tuning or gp_autotune
@@ -142,6 +162,11 @@ struct LocArgs {
   const LocCell *cell;      // PIP: [ncells]
   const int32_t *sub;       //   answer (>= -1) or -(first slot + 2)
   const double4 *slot;      //   lists: per polygon a header and its elements
+  const LocSegCell *scell;  // P2P: [ncells]
+  const uint32_t *soff;     //   [nsub + 1] first entry
+  const LocEntry *ent;
+  const LocSeg *lseg;       //   [nseg]
+  double D2_next;           // the smallest double above fl(D*D)
 };
 
 // What the build needs beside the grid: the (cell, feature) pairs' cells, the rings and the
@@ -255,6 +280,9 @@ bool uses_locator(const Grid &g, gp_precision prec);  // gp_api.cpp
 // the candidate tests of the points' cells, those over `all` (or null) and the points paired.
 hipError_t launch_locate_pip(const LocArgs &a, const double *px, const double *py, int64_t n,
                              int32_t *out_id, unsigned long long *counts, hipStream_t s);
+hipError_t launch_locate_p2p(const LocArgs &a, const double *px, const double *py, int64_t n,
+                             int32_t *out_id, double *out_dist, unsigned long long *counts,
+                             hipStream_t s);
 hipError_t launch_locate_count(const LocArgs &a, const double *px, const double *py, int64_t n,
                                const int32_t *cand_off, const int64_t *cell_tests,
                                const int64_t *all, unsigned long long *counts, hipStream_t s);

@@ -11,11 +11,12 @@
 //         where a chain of edges right of the subcell begins or ends inside its y band.
 //         Polygons with nothing left are either skipped or end the list (the subcell lies
 //         inside them).  Most subcells have a single answer and no list.
+//   P2P   the segments that can be the nearest within D of some point of the subcell.
 //
 // A query is one kernel: a point per lane finds its subcell and evaluates the few entries
-// left with the FP64 predicates in the definition's operation order, so ids
+// left with the FP64 predicates in the definition's operation order, so ids and distances
 // are those of the definition, whatever the precision form.  No sort, no work items and no
-// scattered result stores: the kernel reads 16 bytes and writes 4 per point in the
+// scattered result stores: the kernel reads 16 bytes and writes 4 or 12 per point in the
 // caller's order, and is bound by the gathers of the index.
 //
 // Every bound of the build is conservative: boxes are padded by more than the rounding of
@@ -391,6 +392,281 @@ __global__ __launch_bounds__(256) void k_loc_pip_sub(
   }
 }
 
+// ------------------------------------------------------------------------- P2P build
+
+// Squared distance from c to the segment a + t d, t in [0, 1]; inv = 1 / |d|^2 (0 for a
+// zero-length segment).  For the build's bounds only.
+__device__ __forceinline__ double seg_dist2(double cx, double cy, double ax, double ay,
+                                            double dx, double dy, double inv) {
+  const double wx = cx - ax, wy = cy - ay;
+  const double t = fmin(fmax(fma(wx, dx, wy * dy) * inv, 0.0), 1.0);
+  const double ex = fma(-t, dx, wx), ey = fma(-t, dy, wy);
+  return fma(ex, ex, ey * ey);
+}
+
+// A segment g can only be the nearest within D of a point p of a box with centre c and
+// half diagonal r when d(c, g) <= min(d(c, u) + 2 r, D + r) for every other segment u:
+// otherwise d(p, g) >= d(c, g) - r > d(c, u) + r >= d(p, u), or > D.  slack is over 100
+// times the rounding of the FP64 distances, here and in the definition.
+__device__ __forceinline__ double keep_limit2(double dmin2, double r, double D, double slack) {
+  const double t = fmin(sqrt(dmin2) + 2.0 * r, D + r) + slack;
+  return t * t;
+}
+
+// Segments of every cell, one wave per cell: the candidates' near-segment ranges laid end
+// to end, 64 segments per step.  EMIT = false: counts and the squared distance of the
+// nearest segment to the cell's centre; EMIT: cnt holds the first entries, writes the
+// segments, ascending.
+template <bool EMIT>
+__global__ __launch_bounds__(256) void k_loc_cell_segs(
+    const int32_t *cand_off, const int2 *near, const double4 *edge64, int32_t ncells, double x0,
+    double y0, double cs, int32_t nx, double r, double D,
+    double slack, uint32_t *cnt, double *cmin, int32_t *list) {
+  __shared__ int32_t win[256 / GP_WAVE][2 * GP_WAVE];
+  int32_t *wseg = win[threadIdx.x / GP_WAVE], *wstart = wseg + GP_WAVE;
+  const uint32_t lane = lane_id();
+  const int32_t nw = (int32_t)(gridDim.x * (blockDim.x / GP_WAVE));
+  for (int32_t c = uniform((int32_t)(blockIdx.x * (blockDim.x / GP_WAVE) + threadIdx.x / GP_WAVE));
+       c < ncells; c += nw) {
+    const int32_t k0 = cand_off[c], k1 = cand_off[c + 1];
+    const double cx = x0 + ((double)(c % nx) + 0.5) * cs, cy = y0 + ((double)(c / nx) + 0.5) * cs;
+    double dmin = EMIT ? cmin[c] : INFINITY;
+    uint32_t n = EMIT ? cnt[c] : 0u;
+    for (int sweep = EMIT ? 1 : 0; sweep < 2; ++sweep) {
+      const double lim2 = keep_limit2(dmin, r, D, slack);
+      for (int32_t kw = k0; kw < k1; kw += GP_WAVE) {
+        const int32_t kk = kw + (int32_t)lane;
+        const int nk = k1 - kw < GP_WAVE ? k1 - kw : GP_WAVE;
+        int32_t s0 = 0, len = 0;
+        if (kk < k1) {
+          const int2 nr = near[kk];
+          s0 = nr.x;
+          len = nr.y - nr.x;
+        }
+        uint32_t inc = (uint32_t)len;
+#pragma unroll
+        for (int off = 1; off < GP_WAVE; off <<= 1) {
+          const uint32_t u = __shfl_up(inc, off, GP_WAVE);
+          if (lane >= (uint32_t)off) inc += u;
+        }
+        const int32_t total = __builtin_amdgcn_readlane((int32_t)inc, GP_WAVE - 1);
+        wave_lds_sync();
+        wseg[lane] = s0;
+        wstart[lane] = (int32_t)inc - len;
+        wave_lds_sync();
+        int w = 0;  // this lane's candidate in the window (its flat indices only grow)
+        for (int32_t F0 = 0; F0 < total; F0 += GP_WAVE) {
+          const int32_t F = F0 + (int32_t)lane;
+          double d2 = INFINITY;
+          int32_t sg = 0;
+          if (F < total) {
+            while (w + 1 < nk && wstart[w + 1] <= F) ++w;
+            sg = wseg[w] + (F - wstart[w]);
+            const double4 e = edge64[sg];
+            const double dx = e.z - e.x, dy = e.w - e.y, L2 = dx * dx + dy * dy;
+            d2 = seg_dist2(cx, cy, e.x, e.y, dx, dy, L2 > 0.0 ? 1.0 / L2 : 0.0);
+          }
+          if (sweep == 0) {
+            dmin = fmin(dmin, d2);
+          } else {
+            const bool keep = F < total && !(d2 > lim2);
+            const uint64_t m = ballot(keep);
+            if (EMIT && keep) list[n + (uint32_t)__popcll(m & lanemask_lt())] = sg;
+            n += (uint32_t)__popcll(m);
+          }
+        }
+      }
+      if (sweep == 0)
+        for (int off = 32; off > 0; off >>= 1) dmin = fmin(dmin, __shfl_xor(dmin, off, GP_WAVE));
+    }
+    if (!EMIT && lane == 0) {
+      cnt[c] = n;
+      cmin[c] = dmin;
+    }
+  }
+}
+
+// Subdivision of a cell of n segments: k such that n / k is about `target` (segments per
+// subcell fall like 1 / k where D does not bound them).
+__device__ __forceinline__ uint32_t p2p_shape(uint32_t n, uint32_t target, uint32_t cap) {
+  uint32_t m = 0;
+  while (m < cap && (n >> m) > target) ++m;
+  return m;
+}
+
+// reach of a cell: no point of it has its nearest segment within D farther away.
+// cost[0] += subcells, cost[1] += subcells * segments, cost[2] += expected entries,
+// cost[3] += groups of the list builder.
+__global__ __launch_bounds__(256) void k_loc_p2p_cells(const uint32_t *first, const double *cmin,
+                                                       int32_t ncells, double r, double D,
+                                                       double slack, uint32_t target,
+                                                       uint32_t cap, uint32_t *nsub,
+                                                       LocSegCell *cell,
+                                                       unsigned long long *cost) {
+  unsigned long long s0 = 0, s1 = 0, s2 = 0, s3 = 0;
+  for (int32_t c = blockIdx.x * blockDim.x + threadIdx.x; c <= ncells;
+       c += gridDim.x * blockDim.x) {
+    if (c < ncells) {
+      const uint32_t n = first[c + 1] - first[c];
+      const uint32_t m = p2p_shape(n, target, cap);
+      const uint32_t q = n ? 1u << (2 * m) : 0u;
+      nsub[c] = q;
+      cell[c].m = n ? m : LOC_CONST;
+      cell[c].reach = fmin(sqrt(cmin[c]) + r, D) + slack;
+      s0 += q;
+      s1 += (unsigned long long)q * n;
+      s2 += (unsigned long long)n << m;
+      s3 += n ? group_count(m) : 0u;
+    } else {
+      nsub[c] = 0;
+    }
+  }
+  for (int off = 32; off > 0; off >>= 1) {
+    s0 += __shfl_xor(s0, off, GP_WAVE);
+    s1 += __shfl_xor(s1, off, GP_WAVE);
+    s2 += __shfl_xor(s2, off, GP_WAVE);
+    s3 += __shfl_xor(s3, off, GP_WAVE);
+  }
+  if (lane_id() == 0 && s0) {
+    atomicAdd(cost, s0);
+    atomicAdd(cost + 1, s1);
+    atomicAdd(cost + 2, s2);
+    atomicAdd(cost + 3, s3);
+  }
+}
+
+// Segments by value with their polyline, one 64-byte line each.
+__global__ __launch_bounds__(256) void k_loc_segments(const int32_t *eoff, int32_t nf,
+                                                      const double4 *edge64, LocSeg *seg) {
+  const int32_t nw = (int32_t)(gridDim.x * (blockDim.x / GP_WAVE));
+  for (int32_t f = (int32_t)(blockIdx.x * (blockDim.x / GP_WAVE) + threadIdx.x / GP_WAVE); f < nf;
+       f += nw)
+    for (int32_t e = eoff[f] + (int32_t)lane_id(); e < eoff[f + 1]; e += GP_WAVE) {
+      seg[e].e = edge64[e];
+      seg[e].f = f;
+    }
+}
+
+// Frame of a cell's entries: the cell widened by its reach on every side, in LOC_UNITS
+// steps.  An entry is the part of its segment inside the frame, endpoints rounded to whole
+// steps: for a point of the cell that distance is within 0.71 steps of the segment's
+// wherever the segment's nearest point is inside the frame, and at least the reach
+// otherwise, when the segment cannot be the answer.
+constexpr double LOC_UNITS = 65535.0;
+
+__device__ __forceinline__ uint2 quantised(const double4 e, double ox, double oy, double side) {
+  const double dx = e.z - e.x, dy = e.w - e.y;
+  double t0 = 0.0, t1 = 1.0;
+  bool in = true;
+  auto clip = [&](double q, double d) {  // keeps q + t d >= 0
+    if (d == 0.0) {
+      in &= q >= 0.0;
+    } else {
+      const double t = -q / d;
+      if (d > 0.0) t0 = fmax(t0, t);
+      else t1 = fmin(t1, t);
+    }
+  };
+  clip(e.x - ox, dx);
+  clip(ox + side - e.x, -dx);
+  clip(e.y - oy, dy);
+  clip(oy + side - e.y, -dy);
+  if (!in || !(t0 <= t1)) return make_uint2(0u, 0u);  // outside: the frame's corner
+  const double f = LOC_UNITS / side;
+  auto q = [&](double v) { return (uint32_t)fmin(fmax(v * f + 0.5, 0.0), LOC_UNITS); };
+  // an endpoint inside is taken as it is
+  const double ax = t0 > 0.0 ? e.x + t0 * dx : e.x, ay = t0 > 0.0 ? e.y + t0 * dy : e.y;
+  const double bx = t1 < 1.0 ? e.x + t1 * dx : e.z, by = t1 < 1.0 ? e.y + t1 * dy : e.w;
+  return make_uint2(q(ax - ox) | q(ay - oy) << 16, q(bx - ox) | q(by - oy) << 16);
+}
+
+// Lists of the subcells, one wave per group, lanes over its subcells.  The cell's segments
+// pass 64 at a time, a lane each, and those that cannot be the nearest anywhere in the
+// group (by the same rule, with the group's box) are dropped; the rest are broadcast
+// through LDS.  EMIT = false: entries per subcell in cnt and the subcells' limits in lim;
+// EMIT: cnt holds the first entries.
+template <bool EMIT>
+__global__ __launch_bounds__(256) void k_loc_sub_segs(
+    const uint32_t *first, const int32_t *list, const double4 *edge64, const int2 *group,
+    uint32_t ngroups, const LocSegCell *cell, double x0, double y0, double cs, int32_t nx,
+    double pad, double D, double slack, uint32_t *cnt, double *lim, LocEntry *ent) {
+  __shared__ double4 sa[256 / GP_WAVE][GP_WAVE];  // a.x, a.y, d.x, d.y
+  __shared__ double si[256 / GP_WAVE][GP_WAVE];   // 1 / |d|^2
+  __shared__ LocEntry sl[256 / GP_WAVE][GP_WAVE];
+  const int wave = (int)(threadIdx.x / GP_WAVE);
+  const uint32_t lane = lane_id();
+  const uint32_t w = (uint32_t)uniform((int32_t)(blockIdx.x * (blockDim.x / GP_WAVE)) + wave);
+  if (w >= ngroups) return;
+  const int2 gr = group[w];
+  const int32_t c = uniform(gr.x);
+  const LocSegCell ce = cell[c];
+  const GroupLane g = group_lane(ce.m, uniform(gr.y));
+  const double a = cs / (double)(1u << ce.m), gs = (double)g.gw * a;
+  constexpr double kHalfDiag = 0.70710678118654757 * (1.0 + 0x1p-40);
+  const double r = kHalfDiag * (a + 2.0 * pad), rg = kHalfDiag * (gs + 2.0 * pad);
+  const double ox = x0 + (double)(c % nx) * cs, oy = y0 + (double)(c / nx) * cs;
+  const double gx = ox + (double)g.gx * a + 0.5 * gs, gy = oy + (double)g.gy * a + 0.5 * gs;
+  const double px = ox + ((double)g.sx + 0.5) * a, py = oy + ((double)g.sy + 0.5) * a;
+  const uint32_t at = ce.base + ((uint32_t)g.sy << ce.m) + (uint32_t)g.sx;
+  const uint32_t l0 = first[c], l1 = first[c + 1];
+  // the group's limit
+  double gmin = INFINITY;
+  for (uint32_t l = l0 + lane; l < l1; l += GP_WAVE) {
+    const double4 e = edge64[list[l]];
+    const double dx = e.z - e.x, dy = e.w - e.y, L2 = dx * dx + dy * dy;
+    gmin = fmin(gmin, seg_dist2(gx, gy, e.x, e.y, dx, dy, L2 > 0.0 ? 1.0 / L2 : 0.0));
+  }
+  for (int off = 32; off > 0; off >>= 1) gmin = fmin(gmin, __shfl_xor(gmin, off, GP_WAVE));
+  const double glim2 = keep_limit2(gmin, rg, D, slack);
+  uint32_t n = EMIT && g.act ? cnt[at] : 0u;
+  double dmin = INFINITY, lim2 = EMIT && g.act ? lim[at] : 0.0;
+  for (int sweep = EMIT ? 1 : 0; sweep < 2; ++sweep) {
+    if (!EMIT && sweep == 1) lim2 = keep_limit2(dmin, r, D, slack);
+    for (uint32_t l = l0; l < l1; l += GP_WAVE) {
+      bool use = false;
+      int32_t sg = 0;
+      double4 e;
+      double dx = 0.0, dy = 0.0, inv = 0.0;
+      if (l + lane < l1) {
+        sg = list[l + lane];
+        e = edge64[sg];
+        dx = e.z - e.x;
+        dy = e.w - e.y;
+        const double L2 = dx * dx + dy * dy;
+        inv = L2 > 0.0 ? 1.0 / L2 : 0.0;
+        use = !(seg_dist2(gx, gy, e.x, e.y, dx, dy, inv) > glim2);
+      }
+      const uint64_t mk = ballot(use);
+      wave_lds_sync();
+      if (use) {
+        const int q = (int)__popcll(mk & lanemask_lt());
+        sa[wave][q] = make_double4(e.x, e.y, dx, dy);
+        si[wave][q] = inv;
+        if (EMIT) {
+          const uint2 u = quantised(e, ox - ce.reach, oy - ce.reach, cs + 2.0 * ce.reach);
+          sl[wave][q] = LocEntry{u.x, u.y, sg};
+        }
+      }
+      wave_lds_sync();
+      const int nu = (int)__popcll(mk);
+      for (int q = 0; q < nu; ++q) {
+        const double4 v = sa[wave][q];
+        const double d2 = seg_dist2(px, py, v.x, v.y, v.z, v.w, si[wave][q]);
+        if (sweep == 0) {
+          dmin = fmin(dmin, d2);
+        } else if (!(d2 > lim2)) {
+          if (EMIT && g.act) ent[n] = sl[wave][q];
+          ++n;
+        }
+      }
+    }
+  }
+  if (!EMIT && g.act) {
+    cnt[at] = n;
+    lim[at] = lim2;
+  }
+}
+
 // ------------------------------------------------------------------------- queries
 
 // The point's cell, as the pairing computes it (-1 when unpaired), and its place in the
@@ -456,6 +732,105 @@ __global__ __launch_bounds__(256) void k_locate_pip(LocArgs a, const double *px,
       }
     }
     out_id[i] = ans;
+  }
+}
+
+// FP64 squared distance in the definition's operation order; a perpendicular quotient is
+// divided out only where it can still come below `best` (cc >= fl(best * L2) (1 + 2^-49)
+// implies cc / L2 > best).
+__device__ __forceinline__ double exact_d2(double x, double y, const double4 r, double best) {
+  const double dx = r.z - r.x, dy = r.w - r.y;
+  const double wx = x - r.x, wy = y - r.y;
+  const double L2 = dx * dx + dy * dy;
+  const double t = wx * dx + wy * dy;
+  if (t <= 0.0) return wx * wx + wy * wy;
+  if (t >= L2) {
+    const double ex = x - r.z, ey = y - r.w;
+    return ex * ex + ey * ey;
+  }
+  const double cr = wx * dy - wy * dx;
+  const double cc = cr * cr;
+  return cc < (best * L2) * (1.0 + 0x1p-49) ? cc / L2 : INFINITY;
+}
+
+// Squared distance to an entry, in steps of its frame: FP32 on whole numbers below 2^16.
+// With the entry's rounding (0.71 steps), the point's and the evaluation's (under 0.1), the
+// distance is within LOC_ERR steps of the segment's.
+constexpr float LOC_ERR = 1.0f;
+
+__device__ __forceinline__ float entry_d2(float px, float py, uint32_t a, uint32_t b) {
+  const float ax = (float)(a & 0xffffu), ay = (float)(a >> 16);
+  const float dx = (float)(b & 0xffffu) - ax, dy = (float)(b >> 16) - ay;
+  const float wx = px - ax, wy = py - ay;
+  const float L2 = fmaxf(fmaf(dx, dx, dy * dy), 1.0f);  // 0 or at least 1
+  const float t = __builtin_amdgcn_fmed3f(
+      fmaf(wx, dx, wy * dy) * __builtin_amdgcn_rcpf(L2), 0.0f, 1.0f);
+  const float ex = fmaf(-t, dx, wx), ey = fmaf(-t, dy, wy);
+  return fmaf(ex, ex, ey * ey);
+}
+
+// One point per lane: the FP32 distances of its subcell's entries keep the two nearest (and
+// the third's distance); the entries within twice the error of the nearest, one as a rule,
+// are decided by their exact distances (smaller distance, then smaller polyline).  Bound by
+// the gathers of the lists (200M points: 5.4 L2 lines missed and 27 requested a point).
+// Road map of 5.3M vertices: 200M points 167 -> 31.8 ms against the tiled refinement, 20M
+// with segment lists 5.98 -> 3.39 ms, 1,500 points 0.58 -> 0.012 ms.
+__global__ __launch_bounds__(256) void k_locate_p2p(LocArgs a, const double *px,
+                                                    const double *py, int64_t n,
+                                                    int32_t *out_id, double *out_dist,
+                                                    unsigned long long *counts) {
+  reset_counts(counts);
+  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
+       i += (int64_t)gridDim.x * blockDim.x) {
+    const double x = px[i], y = py[i];
+    double ux, uy;
+    const int32_t c = locate_cell(a, x, y, ux, uy);
+    double best = a.D2_next;  // accept d2 <= fl(D*D); later only strictly smaller
+    int32_t id = -1;
+    if (c >= 0) {
+      const LocSegCell ce = a.scell[c];
+      if (ce.m != LOC_CONST) {
+        const uint32_t s = subcell(ce.base, ce.m, ux, uy);
+        const uint32_t j0 = a.soff[s], j1 = a.soff[s + 1];
+        const double f = LOC_UNITS / (a.cs + 2.0 * ce.reach);
+        const float qx = (float)((ux * a.cs + ce.reach) * f);
+        const float qy = (float)((uy * a.cs + ce.reach) * f);
+        float b1 = INFINITY, b2 = INFINITY, b3 = INFINITY;
+        int32_t i1 = -1, i2 = -1;
+        for (uint32_t j = j0; j < j1; ++j) {
+          const LocEntry e = a.ent[j];
+          const float d = entry_d2(qx, qy, e.a, e.b);
+          b3 = __builtin_amdgcn_fmed3f(d, b2, b3);
+          i2 = d < b1 ? i1 : d < b2 ? e.seg : i2;
+          b2 = __builtin_amdgcn_fmed3f(d, b1, b2);
+          i1 = d < b1 ? e.seg : i1;
+          b1 = fminf(b1, d);
+        }
+        auto take = [&](int32_t sg) {
+          const LocSeg *g = a.lseg + sg;
+          const double d2 = exact_d2(x, y, g->e, a.D2_next);
+          const int32_t fl = g->f;
+          if (d2 < best || (d2 == best && fl < id)) {
+            best = d2;
+            id = fl;
+          }
+        };
+        // the error holds for distances, and 2^-20 covers the squares' and roots' rounding
+        const float lim = (__builtin_amdgcn_sqrtf(b1) + 2.0f * LOC_ERR) * (1.0f + 0x1p-20f);
+        const float lim2 = lim * lim;
+        if (b3 <= lim2) {
+          for (uint32_t j = j0; j < j1; ++j) {
+            const LocEntry e = a.ent[j];
+            if (entry_d2(qx, qy, e.a, e.b) <= lim2) take(e.seg);
+          }
+        } else {
+          if (i1 >= 0) take(i1);
+          if (b2 <= lim2) take(i2);
+        }
+      }
+    }
+    out_id[i] = id;
+    out_dist[i] = id >= 0 ? sqrt(best) : INFINITY;
   }
 }
 
@@ -562,9 +937,47 @@ static hipError_t launch_loc_pip_sub(const Grid &g, const int2 *group, uint32_t 
          elem, cell, g.x0, g.y0, g.cs, g.nx, pad, cnt, slot, sub);
 }
 
+static hipError_t launch_loc_cell_segs(const Grid &g, double r, double slack, uint32_t *cnt,
+                                double *cmin, int32_t *list, hipStream_t s) {
+  const unsigned b = blocks_for(g.ncells, 4, 65536);
+  if (list)
+    LAUNCH(k_loc_cell_segs<true>, b, 256, g.d_cand_off, g.d_near, g.d_edge64, g.ncells, g.x0, g.y0, g.cs, g.nx, r, g.D, slack, cnt, cmin, list);
+  LAUNCH(k_loc_cell_segs<false>, b, 256, g.d_cand_off, g.d_near, g.d_edge64, g.ncells, g.x0, g.y0, g.cs, g.nx, r, g.D, slack, cnt, cmin, list);
+}
+
+static hipError_t launch_loc_p2p_cells(const Grid &g, const uint32_t *first, const double *cmin,
+                                       double r, double slack, uint32_t target, uint32_t cap,
+                                       uint32_t *nsub, LocSegCell *cell,
+                                       unsigned long long *cost, hipStream_t s) {
+  LAUNCH(k_loc_p2p_cells, blocks_for((int64_t)g.ncells + 1, 256, 8192), 256, first, cmin,
+         g.ncells, r, g.D, slack, target, cap, nsub, cell, cost);
+}
+
+static hipError_t launch_loc_segments(const Grid &g, LocSeg *seg, hipStream_t s) {
+  LAUNCH(k_loc_segments, blocks_for(g.nf, 4, 8192), 256, g.d_eoff, g.nf, g.d_edge64, seg);
+}
+
+static hipError_t launch_loc_sub_segs(const Grid &g, const uint32_t *first, const int32_t *list,
+                                      const int2 *group, uint32_t ngroups,
+                                      const LocSegCell *cell, double pad, double slack,
+                                      uint32_t *cnt, double *lim, LocEntry *ent, hipStream_t s) {
+  const unsigned b = (ngroups + 3) / 4;
+  if (ent)
+    LAUNCH(k_loc_sub_segs<true>, b, 256, first, list, g.d_edge64, group, ngroups, cell, g.x0,
+           g.y0, g.cs, g.nx, pad, g.D, slack, cnt, lim, ent);
+  LAUNCH(k_loc_sub_segs<false>, b, 256, first, list, g.d_edge64, group, ngroups, cell, g.x0,
+         g.y0, g.cs, g.nx, pad, g.D, slack, cnt, lim, ent);
+}
+
 hipError_t launch_locate_pip(const LocArgs &a, const double *px, const double *py, int64_t n,
                              int32_t *out_id, unsigned long long *counts, hipStream_t s) {
   LAUNCH(k_locate_pip, blocks_for(n, 256, 1 << 24), 256, a, px, py, n, out_id, counts);
+}
+
+hipError_t launch_locate_p2p(const LocArgs &a, const double *px, const double *py, int64_t n,
+                             int32_t *out_id, double *out_dist, unsigned long long *counts,
+                             hipStream_t s) {
+  LAUNCH(k_locate_p2p, blocks_for(n, 256, 1 << 24), 256, a, px, py, n, out_id, out_dist, counts);
 }
 
 hipError_t launch_locate_count(const LocArgs &a, const double *px, const double *py, int64_t n,
@@ -579,14 +992,17 @@ hipError_t launch_locate_count(const LocArgs &a, const double *px, const double 
 
 namespace {
 
-// Limits of the index: slots of 32 bytes, tests of the build, and entries per subcell beyond which the tiled refinement, which
+// Limits of the index: slots of 32 bytes (PIP), expected entries of 12 bytes (P2P; the
+// lists may hold twice as many), tests of the build, and entries per subcell beyond which the tiled refinement, which
 // reads a list once for 64 and more points, is the better reader of it.
 constexpr int64_t kMaxSlots = int64_t(1) << 27;     // 4 GiB
+constexpr int64_t kMaxEntries = int64_t(1) << 29;   // 6 GiB
 constexpr int64_t kMaxElems = int64_t(1) << 26;     // 2 GiB while building
 constexpr int64_t kMaxSubcells = int64_t(1) << 27;  // 512 MiB
 constexpr int64_t kMaxCells = int64_t(1) << 26;
 constexpr int64_t kMaxBuildTests = int64_t(1) << 33;
 constexpr int64_t kMaxMeanEntries = 64;
+constexpr uint32_t kLocTarget = 8;  // P2P: entries per subcell aimed at
 
 struct Buf {
   void *p = nullptr;
@@ -685,13 +1101,76 @@ hipError_t build_pip(Grid &g, const LocBuild &b, double pad, hipStream_t s) {
   return hipSuccess;
 }
 
+hipError_t build_p2p(Grid &g, double pad, double slack, hipStream_t s) {
+  const size_t nc = (size_t)g.ncells, nseg = (size_t)g.nedges;
+  Buf cnt, cmin, list, nsub, cell, sum, tmp, soff, ent, seg, subtmp, group, lim;
+  LOC_NEED(cnt.alloc((nc + 1) * 4) && cmin.alloc(nc * 8) && nsub.alloc((nc + 1) * 4) &&
+           cell.alloc(nc * sizeof(LocSegCell)) && sum.alloc(64) &&
+           tmp.alloc(scan_tmp_elems(nc + 1) * 4));
+  const double r = 0.70710678118654757 * (1.0 + 0x1p-40) * (g.cs + 2.0 * pad);
+  int64_t total = 0;
+  LOC_TRY(launch_loc_cell_segs(g, r, slack, cnt.as<uint32_t>(), cmin.as<double>(), nullptr, s));
+  LOC_TRY(scan_counts(cnt.as<uint32_t>(), nc, kMaxEntries, sum, tmp.as<uint32_t>(), &total, s));
+  LOC_NEED(total <= kMaxEntries && list.alloc((size_t)total * 4));
+  if (total)
+    LOC_TRY(launch_loc_cell_segs(g, r, slack, cnt.as<uint32_t>(), cmin.as<double>(),
+                                 list.as<int32_t>(), s));
+  unsigned long long cost[4] = {0, 0, 0, 0};
+  for (uint32_t target = kLocTarget;; target *= 2) {
+    LOC_TRY(launch_fill_u32(sum.as<uint32_t>(), 0u, 8, s));
+    LOC_TRY(launch_loc_p2p_cells(g, cnt.as<uint32_t>(), cmin.as<double>(), r, slack + pad, target,
+                                 5u, nsub.as<uint32_t>(), cell.as<LocSegCell>(),
+                                 sum.as<unsigned long long>(), s));
+    LOC_TRY(read_back(cost, sum.p, 32, s));
+    if (cost[0] <= (unsigned long long)kMaxSubcells &&
+        cost[1] <= (unsigned long long)kMaxBuildTests &&
+        cost[2] <= (unsigned long long)kMaxEntries)
+      break;
+    LOC_NEED(target < (1u << 30));
+  }
+  const size_t ns = (size_t)cost[0];
+  LOC_TRY(launch_exclusive_scan_u32(nsub.as<uint32_t>(), nsub.as<uint32_t>(), nc + 1,
+                                    tmp.as<uint32_t>(), s));
+  const uint32_t ng = (uint32_t)cost[3];
+  LOC_NEED(group.alloc((size_t)ng * 8) && lim.alloc(ns * 8));
+  LOC_TRY(launch_loc_groups(nsub.as<uint32_t>(), g.ncells, cell.as<LocSegCell>(),
+                            sum.as<uint32_t>(), group.as<int2>(), s));
+  total = 0;
+  LOC_NEED(soff.alloc((ns + 1) * 4) && subtmp.alloc(scan_tmp_elems(ns + 1) * 4) &&
+           seg.alloc(nseg * sizeof(LocSeg)));
+  LOC_TRY(launch_loc_segments(g, seg.as<LocSeg>(), s));
+  if (ns) {
+    LOC_TRY(launch_loc_sub_segs(g, cnt.as<uint32_t>(), list.as<int32_t>(), group.as<int2>(), ng,
+                                cell.as<LocSegCell>(), pad, slack, soff.as<uint32_t>(),
+                                lim.as<double>(), nullptr, s));
+    LOC_TRY(scan_counts(soff.as<uint32_t>(), ns, 2 * kMaxEntries, sum, subtmp.as<uint32_t>(),
+                        &total, s));
+    LOC_NEED(total <= 2 * kMaxEntries && total <= kMaxMeanEntries * (int64_t)ns);
+    LOC_NEED(ent.alloc((size_t)total * sizeof(LocEntry)));
+    LOC_TRY(launch_loc_sub_segs(g, cnt.as<uint32_t>(), list.as<int32_t>(), group.as<int2>(), ng,
+                                cell.as<LocSegCell>(), pad, slack, soff.as<uint32_t>(),
+                                lim.as<double>(), ent.as<LocEntry>(), s));
+  }
+  LOC_TRY(hipStreamSynchronize(s));
+  g.d_loc_scell = cell.take<LocSegCell>();
+  g.d_loc_soff = soff.take<uint32_t>();
+  g.d_loc_ent = ent.take<LocEntry>();
+  g.d_loc_seg = seg.take<LocSeg>();
+  g.loc_bytes = (int64_t)(nc * sizeof(LocSegCell) + (ns + 1) * 4 + nseg * sizeof(LocSeg)) +
+                total * (int64_t)sizeof(LocEntry);
+  return hipSuccess;
+}
+
 }  // namespace
 
 hipError_t build_locator(Grid &g, const LocBuild &b, hipStream_t s) {
   if (g.ncells > kMaxCells || !(b.max_coord < 1e150) || !(g.cs > 1e-140)) return hipSuccess;
+  // P2P: the frames' steps are whole only where a coordinate's rounding is far below one
+  if (g.kind == GP_P2P && !(b.max_coord < g.cs * 0x1p28)) return hipSuccess;
   // pads: as the MBBs', and over 1000 times the rounding of a point's cell and subcell
   const double pad = g.cs * 0x1p-20 + b.max_coord * 0x1p-40;
-  return build_pip(g, b, pad, s);
+  if (g.kind == GP_PIP) return build_pip(g, b, pad, s);
+  return build_p2p(g, pad, b.max_coord * 0x1p-40 + 0x1p-500, s);
 }
 
 LocArgs locator_args(const Grid &g) {
@@ -704,6 +1183,11 @@ LocArgs locator_args(const Grid &g) {
   a.cell = g.d_loc_cell;
   a.sub = g.d_loc_sub;
   a.slot = g.d_loc_slot;
+  a.soff = g.d_loc_soff;
+  a.scell = g.d_loc_scell;
+  a.ent = g.d_loc_ent;
+  a.lseg = g.d_loc_seg;
+  a.D2_next = nextafter(g.D2, INFINITY);
   return a;
 }
 
