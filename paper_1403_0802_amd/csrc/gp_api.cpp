@@ -577,7 +577,7 @@ extern "C" void gp_grid_free(gp_grid *g) {
   (void)hipFree(g->d_loc_soff);
   (void)hipFree(g->d_loc_seg);
   (void)hipFree(g->d_loc_scell);
-  (void)hipFree(g->d_loc_ent);
+  (void)hipFree(g->d_loc_block);
   delete g;
 }
 

@@ -93,16 +93,21 @@ struct LocCell {
   uint32_t base, m;
 };
 // Locator, P2P: a cell (first subcell, log2 subcells per side or 0xff without segments, and
-// its reach), an entry of a subcell's list (endpoints a and b, x | y << 16 in steps of the
-// cell's frame, and the segment) and a segment by value with its polyline.
+// its reach), a block of a subcell's list (entries with endpoints a and b, x | y << 16 in
+// steps of the cell's frame, and the segment, -1 where the last block has none; rest, a lower
+// bound in steps for the later entries' distance to the subcell's centre, +inf in the last
+// block) and a segment by value with its polyline.  An empty list is one block without segments.
+constexpr int LOC_ENTRIES = 5;
 struct alignas(16) LocSegCell {
   uint32_t base, m;
   double reach;
 };
-struct LocEntry {
-  uint32_t a, b;
-  int32_t seg;
+struct alignas(64) LocBlock {
+  uint32_t a[LOC_ENTRIES], b[LOC_ENTRIES];
+  int32_t seg[LOC_ENTRIES];
+  float rest;
 };
+static_assert(sizeof(LocBlock) == 64, "one aligned 64-byte line");
 struct alignas(64) LocSeg {
   double4 e;
   int32_t f;
@@ -147,7 +152,7 @@ struct Grid {
   double4 *d_loc_slot;
   uint32_t *d_loc_soff;   // P2P
   LocSegCell *d_loc_scell;
-  LocEntry *d_loc_ent;
+  LocBlock *d_loc_block;
   LocSeg *d_loc_seg;
   int64_t loc_bytes;
   gp_tuning tune[2];
@@ -163,8 +168,8 @@ struct LocArgs {
   const int32_t *sub;       //   answer (>= -1) or -(first slot + 2)
   const double4 *slot;      //   lists: per polygon a header and its elements
   const LocSegCell *scell;  // P2P: [ncells]
-  const uint32_t *soff;     //   [nsub + 1] first entry
-  const LocEntry *ent;
+  const uint32_t *soff;     //   first block of each subcell
+  const LocBlock *block;
   const LocSeg *lseg;       //   [nseg]
   double D2_next;           // the smallest double above fl(D*D)
 };

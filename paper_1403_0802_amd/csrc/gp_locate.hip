@@ -583,16 +583,25 @@ __device__ __forceinline__ uint2 quantised(const double4 e, double ox, double oy
 // Lists of the subcells, one wave per group, lanes over its subcells.  The cell's segments
 // pass 64 at a time, a lane each, and those that cannot be the nearest anywhere in the
 // group (by the same rule, with the group's box) are dropped; the rest are broadcast
-// through LDS.  EMIT = false: entries per subcell in cnt and the subcells' limits in lim;
-// EMIT: cnt holds the first entries.
+// through LDS.  A list is ordered by rings around the subcell's centre, LOC_RINGS of equal
+// width from its nearest segment to its limit, so that a query can stop at the first block
+// whose rings are too far.
+// EMIT = false: blocks per subcell in cnt, the distance of the nearest segment and the
+// squared limit in lim; EMIT: cnt holds the first blocks, and receives `empty`, the block
+// that all empty lists share, where there are none.
+constexpr int LOC_RINGS = 8;
+
 template <bool EMIT>
 __global__ __launch_bounds__(256) void k_loc_sub_segs(
     const uint32_t *first, const int32_t *list, const double4 *edge64, const int2 *group,
     uint32_t ngroups, const LocSegCell *cell, double x0, double y0, double cs, int32_t nx,
-    double pad, double D, double slack, uint32_t *cnt, double *lim, LocEntry *ent) {
+    double pad, double D, double slack, uint32_t *cnt, double2 *lim, LocBlock *block,
+    uint32_t empty) {
   __shared__ double4 sa[256 / GP_WAVE][GP_WAVE];  // a.x, a.y, d.x, d.y
   __shared__ double si[256 / GP_WAVE][GP_WAVE];   // 1 / |d|^2
-  __shared__ LocEntry sl[256 / GP_WAVE][GP_WAVE];
+  __shared__ uint2 sl[256 / GP_WAVE][GP_WAVE];    // the entry
+  __shared__ int32_t sg[256 / GP_WAVE][GP_WAVE];  // the segment
+  __shared__ uint32_t ring[LOC_RINGS + 1][256];   // EMIT: entries before each ring, per lane
   const int wave = (int)(threadIdx.x / GP_WAVE);
   const uint32_t lane = lane_id();
   const uint32_t w = (uint32_t)uniform((int32_t)(blockIdx.x * (blockDim.x / GP_WAVE)) + wave);
@@ -618,18 +627,16 @@ __global__ __launch_bounds__(256) void k_loc_sub_segs(
   }
   for (int off = 32; off > 0; off >>= 1) gmin = fmin(gmin, __shfl_xor(gmin, off, GP_WAVE));
   const double glim2 = keep_limit2(gmin, rg, D, slack);
-  uint32_t n = EMIT && g.act ? cnt[at] : 0u;
-  double dmin = INFINITY, lim2 = EMIT && g.act ? lim[at] : 0.0;
-  for (int sweep = EMIT ? 1 : 0; sweep < 2; ++sweep) {
-    if (!EMIT && sweep == 1) lim2 = keep_limit2(dmin, r, D, slack);
+  // the group's segments, broadcast one by one
+  auto sweep = [&](auto &&meet) {
     for (uint32_t l = l0; l < l1; l += GP_WAVE) {
       bool use = false;
-      int32_t sg = 0;
+      int32_t seg = 0;
       double4 e;
       double dx = 0.0, dy = 0.0, inv = 0.0;
       if (l + lane < l1) {
-        sg = list[l + lane];
-        e = edge64[sg];
+        seg = list[l + lane];
+        e = edge64[seg];
         dx = e.z - e.x;
         dy = e.w - e.y;
         const double L2 = dx * dx + dy * dy;
@@ -643,27 +650,79 @@ __global__ __launch_bounds__(256) void k_loc_sub_segs(
         sa[wave][q] = make_double4(e.x, e.y, dx, dy);
         si[wave][q] = inv;
         if (EMIT) {
-          const uint2 u = quantised(e, ox - ce.reach, oy - ce.reach, cs + 2.0 * ce.reach);
-          sl[wave][q] = LocEntry{u.x, u.y, sg};
+          sl[wave][q] = quantised(e, ox - ce.reach, oy - ce.reach, cs + 2.0 * ce.reach);
+          sg[wave][q] = seg;
         }
       }
       wave_lds_sync();
       const int nu = (int)__popcll(mk);
       for (int q = 0; q < nu; ++q) {
         const double4 v = sa[wave][q];
-        const double d2 = seg_dist2(px, py, v.x, v.y, v.z, v.w, si[wave][q]);
-        if (sweep == 0) {
-          dmin = fmin(dmin, d2);
-        } else if (!(d2 > lim2)) {
-          if (EMIT && g.act) ent[n] = sl[wave][q];
-          ++n;
-        }
+        meet(q, seg_dist2(px, py, v.x, v.y, v.z, v.w, si[wave][q]));
       }
     }
-  }
-  if (!EMIT && g.act) {
-    cnt[at] = n;
-    lim[at] = lim2;
+  };
+  if constexpr (!EMIT) {
+    double dmin = INFINITY;
+    sweep([&](int, double d2) { dmin = fmin(dmin, d2); });
+    const double lim2 = keep_limit2(dmin, r, D, slack);
+    uint32_t n = 0;
+    sweep([&](int, double d2) { n += !(d2 > lim2); });
+    if (g.act) {
+      cnt[at] = (n + LOC_ENTRIES - 1) / LOC_ENTRIES;
+      lim[at] = make_double2(sqrt(dmin), lim2);
+    }
+  } else {
+    const double2 dl = g.act ? lim[at] : make_double2(0.0, 0.0);
+    const double lim2 = dl.y, step = (sqrt(lim2) - dl.x) * (1.0 / LOC_RINGS);
+    double t2[LOC_RINGS];  // squared inner radius of each ring
+#pragma unroll
+    for (int i = 0; i < LOC_RINGS; ++i) {
+      const double t = dl.x + (double)i * step;
+      t2[i] = t * t;
+    }
+    auto ring_of = [&](double d2) {
+      int i = 0;
+#pragma unroll
+      for (int k = 1; k < LOC_RINGS; ++k) i += d2 > t2[k] ? 1 : 0;
+      return i;
+    };
+    const uint32_t tid = threadIdx.x;
+#pragma unroll
+    for (int i = 0; i <= LOC_RINGS; ++i) ring[i][tid] = 0;
+    sweep([&](int, double d2) {
+      if (!(d2 > lim2)) ++ring[ring_of(d2) + 1][tid];
+    });
+#pragma unroll
+    for (int i = 1; i <= LOC_RINGS; ++i) ring[i][tid] += ring[i - 1][tid];
+    const uint32_t n = ring[LOC_RINGS][tid], nb = (n + LOC_ENTRIES - 1) / LOC_ENTRIES;
+    LocBlock *out = g.act ? block + cnt[at] : nullptr;
+    if (g.act && n == 0) cnt[at] = empty;
+    if (g.act) {
+      // a block's `rest` is at most the distance to the centre of any later entry, in steps
+      // of the frame; the last block's ends the list
+      const double f = LOC_UNITS / (cs + 2.0 * ce.reach) * (1.0 - 0x1p-16);
+      for (uint32_t k = 0; k < nb; ++k) {
+        const uint32_t e = (k + 1) * LOC_ENTRIES;
+        int i = 0;
+        while (i + 1 < LOC_RINGS && ring[i + 1][tid] <= e) ++i;
+        out[k].rest = e < n ? (float)((dl.x + (double)i * step) * f) : INFINITY;
+      }
+      for (uint32_t e = n; e < nb * LOC_ENTRIES; ++e) {
+        LocBlock &o = out[e / LOC_ENTRIES];
+        o.a[e % LOC_ENTRIES] = o.b[e % LOC_ENTRIES] = 0u;
+        o.seg[e % LOC_ENTRIES] = -1;
+      }
+    }
+    sweep([&](int q, double d2) {
+      if (g.act && !(d2 > lim2)) {
+        const uint32_t e = ring[ring_of(d2)][tid]++;
+        LocBlock &o = out[e / LOC_ENTRIES];
+        o.a[e % LOC_ENTRIES] = sl[wave][q].x;
+        o.b[e % LOC_ENTRIES] = sl[wave][q].y;
+        o.seg[e % LOC_ENTRIES] = sg[wave][q];
+      }
+    });
   }
 }
 
@@ -790,21 +849,41 @@ __global__ __launch_bounds__(256) void k_locate_p2p(LocArgs a, const double *px,
     if (c >= 0) {
       const LocSegCell ce = a.scell[c];
       if (ce.m != LOC_CONST) {
-        const uint32_t s = subcell(ce.base, ce.m, ux, uy);
-        const uint32_t j0 = a.soff[s], j1 = a.soff[s + 1];
         const double f = LOC_UNITS / (a.cs + 2.0 * ce.reach);
         const float qx = (float)((ux * a.cs + ce.reach) * f);
         const float qy = (float)((uy * a.cs + ce.reach) * f);
+        // distance to the subcell's centre, in steps, and the error of an entry's distance
+        const double k = (double)(1u << ce.m);
+        const float vx = (float)(ux * k - floor(ux * k)) - 0.5f;
+        const float vy = (float)(uy * k - floor(uy * k)) - 0.5f;
+        const float off = __builtin_amdgcn_sqrtf(fmaf(vx, vx, vy * vy)) *
+                              (float)(a.cs * f / k * (1.0 + 0x1p-16)) + LOC_ERR;
         float b1 = INFINITY, b2 = INFINITY, b3 = INFINITY;
         int32_t i1 = -1, i2 = -1;
-        for (uint32_t j = j0; j < j1; ++j) {
-          const LocEntry e = a.ent[j];
-          const float d = entry_d2(qx, qy, e.a, e.b);
+        auto meet = [&](uint32_t ea, uint32_t eb, int32_t seg) {
+          const float d = seg < 0 ? INFINITY : entry_d2(qx, qy, ea, eb);
           b3 = __builtin_amdgcn_fmed3f(d, b2, b3);
-          i2 = d < b1 ? i1 : d < b2 ? e.seg : i2;
+          i2 = d < b1 ? i1 : d < b2 ? seg : i2;
           b2 = __builtin_amdgcn_fmed3f(d, b1, b2);
-          i1 = d < b1 ? e.seg : i1;
+          i1 = d < b1 ? seg : i1;
           b1 = fminf(b1, d);
+        };
+        const uint32_t j0 = a.soff[subcell(ce.base, ce.m, ux, uy)];
+        // no later entry can be the nearest once its distance to the centre exceeds the
+        // point's and the nearest entry's together
+        auto enough = [&](float rest) {
+          return rest > off + __builtin_amdgcn_sqrtf(b1) * (1.0f + 0x1p-20f);
+        };
+        for (const LocBlock *q = a.block + j0;; ++q) {
+          const uint4 w0 = ((const uint4 *)q)[0], w1 = ((const uint4 *)q)[1],
+                      w2 = ((const uint4 *)q)[2], w3 = ((const uint4 *)q)[3];
+          meet(w0.x, w1.y, (int32_t)w2.z);
+          meet(w0.y, w1.z, (int32_t)w2.w);
+          meet(w0.z, w1.w, (int32_t)w3.x);
+          meet(w0.w, w2.x, (int32_t)w3.y);
+          meet(w1.x, w2.y, (int32_t)w3.z);
+          const float rest = __uint_as_float(w3.w);
+          if (rest == INFINITY || enough(rest)) break;
         }
         auto take = [&](int32_t sg) {
           const LocSeg *g = a.lseg + sg;
@@ -819,9 +898,10 @@ __global__ __launch_bounds__(256) void k_locate_p2p(LocArgs a, const double *px,
         const float lim = (__builtin_amdgcn_sqrtf(b1) + 2.0f * LOC_ERR) * (1.0f + 0x1p-20f);
         const float lim2 = lim * lim;
         if (b3 <= lim2) {
-          for (uint32_t j = j0; j < j1; ++j) {
-            const LocEntry e = a.ent[j];
-            if (entry_d2(qx, qy, e.a, e.b) <= lim2) take(e.seg);
+          for (const LocBlock *q = a.block + j0;; ++q) {
+            for (int t = 0; t < LOC_ENTRIES; ++t)
+              if (q->seg[t] >= 0 && entry_d2(qx, qy, q->a[t], q->b[t]) <= lim2) take(q->seg[t]);
+            if (q->rest == INFINITY || enough(q->rest)) break;
           }
         } else {
           if (i1 >= 0) take(i1);
@@ -960,13 +1040,14 @@ static hipError_t launch_loc_segments(const Grid &g, LocSeg *seg, hipStream_t s)
 static hipError_t launch_loc_sub_segs(const Grid &g, const uint32_t *first, const int32_t *list,
                                       const int2 *group, uint32_t ngroups,
                                       const LocSegCell *cell, double pad, double slack,
-                                      uint32_t *cnt, double *lim, LocEntry *ent, hipStream_t s) {
+                                      uint32_t *cnt, double2 *lim, LocBlock *block,
+                                      uint32_t empty, hipStream_t s) {
   const unsigned b = (ngroups + 3) / 4;
-  if (ent)
+  if (block)
     LAUNCH(k_loc_sub_segs<true>, b, 256, first, list, g.d_edge64, group, ngroups, cell, g.x0,
-           g.y0, g.cs, g.nx, pad, g.D, slack, cnt, lim, ent);
+           g.y0, g.cs, g.nx, pad, g.D, slack, cnt, lim, block, empty);
   LAUNCH(k_loc_sub_segs<false>, b, 256, first, list, g.d_edge64, group, ngroups, cell, g.x0,
-         g.y0, g.cs, g.nx, pad, g.D, slack, cnt, lim, ent);
+         g.y0, g.cs, g.nx, pad, g.D, slack, cnt, lim, block, empty);
 }
 
 hipError_t launch_locate_pip(const LocArgs &a, const double *px, const double *py, int64_t n,
@@ -992,11 +1073,12 @@ hipError_t launch_locate_count(const LocArgs &a, const double *px, const double 
 
 namespace {
 
-// Limits of the index: slots of 32 bytes (PIP), expected entries of 12 bytes (P2P; the
-// lists may hold twice as many), tests of the build, and entries per subcell beyond which the tiled refinement, which
+// Limits of the index: slots of 32 bytes (PIP), expected entries and blocks of 5 of them
+// (P2P), tests of the build, and entries per subcell beyond which the tiled refinement, which
 // reads a list once for 64 and more points, is the better reader of it.
 constexpr int64_t kMaxSlots = int64_t(1) << 27;     // 4 GiB
-constexpr int64_t kMaxEntries = int64_t(1) << 29;   // 6 GiB
+constexpr int64_t kMaxEntries = int64_t(1) << 29;
+constexpr int64_t kMaxBlocks = int64_t(1) << 27;    // 8 GiB
 constexpr int64_t kMaxElems = int64_t(1) << 26;     // 2 GiB while building
 constexpr int64_t kMaxSubcells = int64_t(1) << 27;  // 512 MiB
 constexpr int64_t kMaxCells = int64_t(1) << 26;
@@ -1103,7 +1185,7 @@ hipError_t build_pip(Grid &g, const LocBuild &b, double pad, hipStream_t s) {
 
 hipError_t build_p2p(Grid &g, double pad, double slack, hipStream_t s) {
   const size_t nc = (size_t)g.ncells, nseg = (size_t)g.nedges;
-  Buf cnt, cmin, list, nsub, cell, sum, tmp, soff, ent, seg, subtmp, group, lim;
+  Buf cnt, cmin, list, nsub, cell, sum, tmp, soff, block, seg, subtmp, group, lim;
   LOC_NEED(cnt.alloc((nc + 1) * 4) && cmin.alloc(nc * 8) && nsub.alloc((nc + 1) * 4) &&
            cell.alloc(nc * sizeof(LocSegCell)) && sum.alloc(64) &&
            tmp.alloc(scan_tmp_elems(nc + 1) * 4));
@@ -1132,7 +1214,7 @@ hipError_t build_p2p(Grid &g, double pad, double slack, hipStream_t s) {
   LOC_TRY(launch_exclusive_scan_u32(nsub.as<uint32_t>(), nsub.as<uint32_t>(), nc + 1,
                                     tmp.as<uint32_t>(), s));
   const uint32_t ng = (uint32_t)cost[3];
-  LOC_NEED(group.alloc((size_t)ng * 8) && lim.alloc(ns * 8));
+  LOC_NEED(group.alloc((size_t)ng * 8) && lim.alloc(ns * 16));
   LOC_TRY(launch_loc_groups(nsub.as<uint32_t>(), g.ncells, cell.as<LocSegCell>(),
                             sum.as<uint32_t>(), group.as<int2>(), s));
   total = 0;
@@ -1142,22 +1224,25 @@ hipError_t build_p2p(Grid &g, double pad, double slack, hipStream_t s) {
   if (ns) {
     LOC_TRY(launch_loc_sub_segs(g, cnt.as<uint32_t>(), list.as<int32_t>(), group.as<int2>(), ng,
                                 cell.as<LocSegCell>(), pad, slack, soff.as<uint32_t>(),
-                                lim.as<double>(), nullptr, s));
-    LOC_TRY(scan_counts(soff.as<uint32_t>(), ns, 2 * kMaxEntries, sum, subtmp.as<uint32_t>(),
-                        &total, s));
-    LOC_NEED(total <= 2 * kMaxEntries && total <= kMaxMeanEntries * (int64_t)ns);
-    LOC_NEED(ent.alloc((size_t)total * sizeof(LocEntry)));
+                                lim.as<double2>(), nullptr, 0u, s));
+    LOC_TRY(scan_counts(soff.as<uint32_t>(), ns, kMaxBlocks, sum, subtmp.as<uint32_t>(), &total,
+                        s));
+    LOC_NEED(total <= kMaxBlocks && LOC_ENTRIES * total <= kMaxMeanEntries * (int64_t)ns);
+    LOC_NEED(block.alloc((size_t)(total + 1) * sizeof(LocBlock)));
+    uint32_t *last = (uint32_t *)(block.as<LocBlock>() + total);
+    LOC_TRY(launch_fill_u32(last, 0xffffffffu, 15, s));  // no segments
+    LOC_TRY(launch_fill_u32(last + 15, 0x7f800000u, 1, s));  // rest = +inf
     LOC_TRY(launch_loc_sub_segs(g, cnt.as<uint32_t>(), list.as<int32_t>(), group.as<int2>(), ng,
                                 cell.as<LocSegCell>(), pad, slack, soff.as<uint32_t>(),
-                                lim.as<double>(), ent.as<LocEntry>(), s));
+                                lim.as<double2>(), block.as<LocBlock>(), (uint32_t)total, s));
   }
   LOC_TRY(hipStreamSynchronize(s));
   g.d_loc_scell = cell.take<LocSegCell>();
   g.d_loc_soff = soff.take<uint32_t>();
-  g.d_loc_ent = ent.take<LocEntry>();
+  g.d_loc_block = block.take<LocBlock>();
   g.d_loc_seg = seg.take<LocSeg>();
   g.loc_bytes = (int64_t)(nc * sizeof(LocSegCell) + (ns + 1) * 4 + nseg * sizeof(LocSeg)) +
-                total * (int64_t)sizeof(LocEntry);
+                (total + 1) * (int64_t)sizeof(LocBlock);
   return hipSuccess;
 }
 
@@ -1185,7 +1270,7 @@ LocArgs locator_args(const Grid &g) {
   a.slot = g.d_loc_slot;
   a.soff = g.d_loc_soff;
   a.scell = g.d_loc_scell;
-  a.ent = g.d_loc_ent;
+  a.block = g.d_loc_block;
   a.lseg = g.d_loc_seg;
   a.D2_next = nextafter(g.D2, INFINITY);
   return a;
