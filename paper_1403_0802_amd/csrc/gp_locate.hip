@@ -50,6 +50,16 @@ unsigned blocks_for(int64_t n, int64_t per, int64_t cap) {
   return (unsigned)std::max<int64_t>(1, std::min<int64_t>((n + per - 1) / per, cap));
 }
 
+// Place of cell c in the order of the index: tiles of 16 x 16 cells, row by row, and the
+// cells of a tile row by row.  A neighbourhood of cells then lies in few pages, as the
+// address translation of a compute unit needs where points cluster.
+__device__ __forceinline__ int32_t tiled_rank(int32_t c, int32_t nx, int32_t ny) {
+  const int32_t x = c % nx, y = c / nx;
+  const int32_t tx = x & ~15, ty = y & ~15;
+  const int32_t w = nx - tx < 16 ? nx - tx : 16, h = ny - ty < 16 ? ny - ty : 16;
+  return ty * nx + tx * h + (y - ty) * w + (x - tx);
+}
+
 // ------------------------------------------------------------------------- PIP build
 
 // x of the stand-ins for chains of edges right of a subcell: far right of any point (the
@@ -169,11 +179,12 @@ __device__ __forceinline__ uint32_t pip_shape(uint32_t E, uint32_t cap) {
 }
 
 __global__ __launch_bounds__(256) void k_loc_pip_cells(const int32_t *cand_off,
-                                                       const int32_t *cand_id, int32_t ncells,
-                                                       const uint32_t *eoffs, const uint8_t *par,
+                                                       const int32_t *cand_id, int32_t nx,
+                                                       int32_t ny, const uint32_t *eoffs, const uint8_t *par,
                                                        uint32_t cap, uint32_t *nsub,
                                                        LocCell *cell,
                                                        unsigned long long *cost) {
+  const int32_t ncells = nx * ny;
   unsigned long long s0 = 0, s1 = 0, s2 = 0;
   for (int32_t c = blockIdx.x * blockDim.x + threadIdx.x; c <= ncells;
        c += gridDim.x * blockDim.x) {
@@ -191,7 +202,7 @@ __global__ __launch_bounds__(256) void k_loc_pip_cells(const int32_t *cand_off,
       }
       const uint32_t m = pip_shape(E, cap);
       const uint32_t q = E ? 1u << (2 * m) : 0u;
-      nsub[c] = q;
+      nsub[tiled_rank(c, nx, ny)] = q;
       cell[c] = LocCell{(uint32_t)ans, E ? m : LOC_CONST};
       s0 += q;
       s1 += (unsigned long long)q * E;
@@ -214,9 +225,9 @@ __global__ __launch_bounds__(256) void k_loc_pip_cells(const int32_t *cand_off,
 
 // Subcell base of every divided cell, from the scan of nsub.
 template <class Cell>
-__global__ void k_loc_cell_base(const uint32_t *base, int32_t ncells, Cell *cell) {
-  for (int32_t c = blockIdx.x * blockDim.x + threadIdx.x; c < ncells; c += gridDim.x * blockDim.x)
-    if (cell[c].m != LOC_CONST) cell[c].base = base[c];
+__global__ void k_loc_cell_base(const uint32_t *base, int32_t nx, int32_t ny, Cell *cell) {
+  for (int32_t c = blockIdx.x * blockDim.x + threadIdx.x; c < nx * ny; c += gridDim.x * blockDim.x)
+    if (cell[c].m != LOC_CONST) cell[c].base = base[tiled_rank(c, nx, ny)];
 }
 
 // The groups (cell, block), in no particular order.  One atomic per wave.
@@ -498,11 +509,12 @@ __device__ __forceinline__ uint32_t p2p_shape(uint32_t n, uint32_t target, uint3
 // cost[0] += subcells, cost[1] += subcells * segments, cost[2] += expected entries,
 // cost[3] += groups of the list builder.
 __global__ __launch_bounds__(256) void k_loc_p2p_cells(const uint32_t *first, const double *cmin,
-                                                       int32_t ncells, double r, double D,
-                                                       double slack, uint32_t target,
+                                                       int32_t nx, int32_t ny, double r,
+                                                       double D, double slack, uint32_t target,
                                                        uint32_t cap, uint32_t *nsub,
                                                        LocSegCell *cell,
                                                        unsigned long long *cost) {
+  const int32_t ncells = nx * ny;
   unsigned long long s0 = 0, s1 = 0, s2 = 0, s3 = 0;
   for (int32_t c = blockIdx.x * blockDim.x + threadIdx.x; c <= ncells;
        c += gridDim.x * blockDim.x) {
@@ -510,7 +522,7 @@ __global__ __launch_bounds__(256) void k_loc_p2p_cells(const uint32_t *first, co
       const uint32_t n = first[c + 1] - first[c];
       const uint32_t m = p2p_shape(n, target, cap);
       const uint32_t q = n ? 1u << (2 * m) : 0u;
-      nsub[c] = q;
+      nsub[tiled_rank(c, nx, ny)] = q;
       cell[c].m = n ? m : LOC_CONST;
       cell[c].reach = fmin(sqrt(cmin[c]) + r, D) + slack;
       s0 += q;
@@ -535,16 +547,35 @@ __global__ __launch_bounds__(256) void k_loc_p2p_cells(const uint32_t *first, co
   }
 }
 
-// Segments by value with their polyline, one 64-byte line each.
-__global__ __launch_bounds__(256) void k_loc_segments(const int32_t *eoff, int32_t nf,
-                                                      const double4 *edge64, LocSeg *seg) {
+// Segments by value with their polyline, 64 bytes each, in the order of the index's cells (by
+// the cell of the midpoint), so that segments near each other share lines and pages.
+__global__ void k_loc_seg_keys(const double4 *edge64, int32_t n, double x0, double y0, double cs,
+                               int32_t nx, int32_t ny, uint32_t *key) {
+  for (int32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
+    const double4 e = edge64[i];
+    const double fx = floor((0.5 * (e.x + e.z) - x0) / cs), fy = floor((0.5 * (e.y + e.w) - y0) / cs);
+    const int32_t x = (int32_t)fmin(fmax(fx, 0.0), (double)(nx - 1));
+    const int32_t y = (int32_t)fmin(fmax(fy, 0.0), (double)(ny - 1));
+    key[i] = (uint32_t)tiled_rank(y * nx + x, nx, ny);
+  }
+}
+
+__global__ __launch_bounds__(256) void k_loc_polylines(const int32_t *eoff, int32_t nf, int32_t *f) {
   const int32_t nw = (int32_t)(gridDim.x * (blockDim.x / GP_WAVE));
-  for (int32_t f = (int32_t)(blockIdx.x * (blockDim.x / GP_WAVE) + threadIdx.x / GP_WAVE); f < nf;
-       f += nw)
-    for (int32_t e = eoff[f] + (int32_t)lane_id(); e < eoff[f + 1]; e += GP_WAVE) {
-      seg[e].e = edge64[e];
-      seg[e].f = f;
-    }
+  for (int32_t q = (int32_t)(blockIdx.x * (blockDim.x / GP_WAVE) + threadIdx.x / GP_WAVE); q < nf;
+       q += nw)
+    for (int32_t e = eoff[q] + (int32_t)lane_id(); e < eoff[q + 1]; e += GP_WAVE) f[e] = q;
+}
+
+// place[old] = new, from the sorted order.
+__global__ void k_loc_segments(const uint32_t *order, const int32_t *f, const double4 *edge64,
+                               int32_t n, LocSeg *seg, int32_t *place) {
+  for (int32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
+    const int32_t o = (int32_t)order[i];
+    seg[i].e = edge64[o];
+    seg[i].f = f[o];
+    place[o] = i;
+  }
 }
 
 // Frame of a cell's entries: the cell widened by its reach on every side, in LOC_UNITS
@@ -595,8 +626,8 @@ template <bool EMIT>
 __global__ __launch_bounds__(256) void k_loc_sub_segs(
     const uint32_t *first, const int32_t *list, const double4 *edge64, const int2 *group,
     uint32_t ngroups, const LocSegCell *cell, double x0, double y0, double cs, int32_t nx,
-    double pad, double D, double slack, uint32_t *cnt, double2 *lim, LocBlock *block,
-    uint32_t empty) {
+    double pad, double D, double slack, const int32_t *place, uint32_t *cnt, double2 *lim,
+    LocBlock *block, uint32_t empty) {
   __shared__ double4 sa[256 / GP_WAVE][GP_WAVE];  // a.x, a.y, d.x, d.y
   __shared__ double si[256 / GP_WAVE][GP_WAVE];   // 1 / |d|^2
   __shared__ uint2 sl[256 / GP_WAVE][GP_WAVE];    // the entry
@@ -651,7 +682,7 @@ __global__ __launch_bounds__(256) void k_loc_sub_segs(
         si[wave][q] = inv;
         if (EMIT) {
           sl[wave][q] = quantised(e, ox - ce.reach, oy - ce.reach, cs + 2.0 * ce.reach);
-          sg[wave][q] = seg;
+          sg[wave][q] = place[seg];
         }
       }
       wave_lds_sync();
@@ -989,20 +1020,20 @@ static hipError_t launch_loc_pip_cells(const Grid &g, const uint32_t *eoffs, con
                                        uint32_t cap, uint32_t *nsub, LocCell *cell,
                                        unsigned long long *cost, hipStream_t s) {
   LAUNCH(k_loc_pip_cells, blocks_for((int64_t)g.ncells + 1, 256, 8192), 256, g.d_cand_off,
-         g.d_cand_id, g.ncells, eoffs, par, cap, nsub, cell, cost);
+         g.d_cand_id, g.nx, g.ny, eoffs, par, cap, nsub, cell, cost);
 }
 
 // Subcell bases of the cells from the scan of nsub, and their groups; *n is zeroed here.
 template <class Cell>
-static hipError_t launch_loc_groups(const uint32_t *base, int32_t ncells, Cell *cell,
-                                    uint32_t *n, int2 *group, hipStream_t s) {
-  const unsigned b = blocks_for(ncells, 256, 8192);
+static hipError_t launch_loc_groups(const Grid &g, const uint32_t *base, Cell *cell, uint32_t *n,
+                                    int2 *group, hipStream_t s) {
+  const unsigned b = blocks_for(g.ncells, 256, 8192);
   hipError_t e = launch_fill_u32(n, 0u, 1, s);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_loc_cell_base<Cell>, dim3(b), dim3(256), 0, s, base, ncells, cell);
+  hipLaunchKernelGGL(k_loc_cell_base<Cell>, dim3(b), dim3(256), 0, s, base, g.nx, g.ny, cell);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
-  LAUNCH(k_loc_groups<Cell>, b, 256, cell, ncells, n, group);
+  LAUNCH(k_loc_groups<Cell>, b, 256, cell, g.ncells, n, group);
 }
 
 static hipError_t launch_loc_pip_sub(const Grid &g, const int2 *group, uint32_t ngroups,
@@ -1030,24 +1061,35 @@ static hipError_t launch_loc_p2p_cells(const Grid &g, const uint32_t *first, con
                                        uint32_t *nsub, LocSegCell *cell,
                                        unsigned long long *cost, hipStream_t s) {
   LAUNCH(k_loc_p2p_cells, blocks_for((int64_t)g.ncells + 1, 256, 8192), 256, first, cmin,
-         g.ncells, r, g.D, slack, target, cap, nsub, cell, cost);
+         g.nx, g.ny, r, g.D, slack, target, cap, nsub, cell, cost);
 }
 
-static hipError_t launch_loc_segments(const Grid &g, LocSeg *seg, hipStream_t s) {
-  LAUNCH(k_loc_segments, blocks_for(g.nf, 4, 8192), 256, g.d_eoff, g.nf, g.d_edge64, seg);
+static hipError_t launch_loc_seg_keys(const Grid &g, uint32_t *key, hipStream_t s) {
+  LAUNCH(k_loc_seg_keys, blocks_for(g.nedges, 256, 8192), 256, g.d_edge64, g.nedges, g.x0, g.y0,
+         g.cs, g.nx, g.ny, key);
+}
+
+static hipError_t launch_loc_polylines(const Grid &g, int32_t *f, hipStream_t s) {
+  LAUNCH(k_loc_polylines, blocks_for(g.nf, 4, 8192), 256, g.d_eoff, g.nf, f);
+}
+
+static hipError_t launch_loc_segments(const Grid &g, const uint32_t *order, const int32_t *f,
+                                      LocSeg *seg, int32_t *place, hipStream_t s) {
+  LAUNCH(k_loc_segments, blocks_for(g.nedges, 256, 8192), 256, order, f, g.d_edge64, g.nedges,
+         seg, place);
 }
 
 static hipError_t launch_loc_sub_segs(const Grid &g, const uint32_t *first, const int32_t *list,
                                       const int2 *group, uint32_t ngroups,
                                       const LocSegCell *cell, double pad, double slack,
-                                      uint32_t *cnt, double2 *lim, LocBlock *block,
+                                      const int32_t *place, uint32_t *cnt, double2 *lim, LocBlock *block,
                                       uint32_t empty, hipStream_t s) {
   const unsigned b = (ngroups + 3) / 4;
   if (block)
     LAUNCH(k_loc_sub_segs<true>, b, 256, first, list, g.d_edge64, group, ngroups, cell, g.x0,
-           g.y0, g.cs, g.nx, pad, g.D, slack, cnt, lim, block, empty);
+           g.y0, g.cs, g.nx, pad, g.D, slack, place, cnt, lim, block, empty);
   LAUNCH(k_loc_sub_segs<false>, b, 256, first, list, g.d_edge64, group, ngroups, cell, g.x0,
-         g.y0, g.cs, g.nx, pad, g.D, slack, cnt, lim, block, empty);
+         g.y0, g.cs, g.nx, pad, g.D, slack, place, cnt, lim, block, empty);
 }
 
 hipError_t launch_locate_pip(const LocArgs &a, const double *px, const double *py, int64_t n,
@@ -1160,7 +1202,7 @@ hipError_t build_pip(Grid &g, const LocBuild &b, double pad, hipStream_t s) {
                                     tmp.as<uint32_t>(), s));
   const uint32_t ng = (uint32_t)cost[2];
   LOC_NEED(group.alloc((size_t)ng * 8));
-  LOC_TRY(launch_loc_groups(nsub.as<uint32_t>(), g.ncells, cell.as<LocCell>(),
+  LOC_TRY(launch_loc_groups(g, nsub.as<uint32_t>(), cell.as<LocCell>(),
                             sum.as<uint32_t>(), group.as<int2>(), s));
   total = 0;
   LOC_NEED(sub.alloc(ns * 4) && scnt.alloc((ns + 1) * 4) &&
@@ -1185,7 +1227,7 @@ hipError_t build_pip(Grid &g, const LocBuild &b, double pad, hipStream_t s) {
 
 hipError_t build_p2p(Grid &g, double pad, double slack, hipStream_t s) {
   const size_t nc = (size_t)g.ncells, nseg = (size_t)g.nedges;
-  Buf cnt, cmin, list, nsub, cell, sum, tmp, soff, block, seg, subtmp, group, lim;
+  Buf cnt, cmin, list, nsub, cell, sum, tmp, soff, block, seg, subtmp, group, lim, place;
   LOC_NEED(cnt.alloc((nc + 1) * 4) && cmin.alloc(nc * 8) && nsub.alloc((nc + 1) * 4) &&
            cell.alloc(nc * sizeof(LocSegCell)) && sum.alloc(64) &&
            tmp.alloc(scan_tmp_elems(nc + 1) * 4));
@@ -1215,15 +1257,36 @@ hipError_t build_p2p(Grid &g, double pad, double slack, hipStream_t s) {
                                     tmp.as<uint32_t>(), s));
   const uint32_t ng = (uint32_t)cost[3];
   LOC_NEED(group.alloc((size_t)ng * 8) && lim.alloc(ns * 16));
-  LOC_TRY(launch_loc_groups(nsub.as<uint32_t>(), g.ncells, cell.as<LocSegCell>(),
+  LOC_TRY(launch_loc_groups(g, nsub.as<uint32_t>(), cell.as<LocSegCell>(),
                             sum.as<uint32_t>(), group.as<int2>(), s));
   total = 0;
   LOC_NEED(soff.alloc((ns + 1) * 4) && subtmp.alloc(scan_tmp_elems(ns + 1) * 4) &&
            seg.alloc(nseg * sizeof(LocSeg)));
-  LOC_TRY(launch_loc_segments(g, seg.as<LocSeg>(), s));
+  LOC_NEED(place.alloc(nseg * 4));
+  {
+    Buf kA, kB, vA, vB, hist, htmp, poly;
+    LOC_NEED(kA.alloc(nseg * 4) && kB.alloc(nseg * 4) && vA.alloc(nseg * 4) &&
+             vB.alloc(nseg * 4) && poly.alloc(nseg * 4) &&
+             hist.alloc(radix_hist_elems(nseg) * 4) &&
+             htmp.alloc(scan_tmp_elems(radix_hist_elems(nseg)) * 4));
+    uint32_t *keys = nullptr, *order = nullptr;
+    int bits = 1;
+    while (bits < 31 && (1 << bits) < g.ncells) ++bits;
+    if (nseg) {
+      LOC_TRY(launch_loc_seg_keys(g, kA.as<uint32_t>(), s));
+      LOC_TRY(launch_loc_polylines(g, poly.as<int32_t>(), s));
+      LOC_TRY(launch_radix_sort(kA.as<uint32_t>(), kB.as<uint32_t>(), vA.as<uint32_t>(),
+                                vB.as<uint32_t>(), nseg, bits, true, hist.as<uint32_t>(),
+                                htmp.as<uint32_t>(), s, &keys, &order));
+      LOC_TRY(launch_loc_segments(g, order, poly.as<int32_t>(), seg.as<LocSeg>(),
+                                  place.as<int32_t>(), s));
+    }
+    LOC_TRY(hipStreamSynchronize(s));  // before the sort's buffers go
+  }
   if (ns) {
     LOC_TRY(launch_loc_sub_segs(g, cnt.as<uint32_t>(), list.as<int32_t>(), group.as<int2>(), ng,
-                                cell.as<LocSegCell>(), pad, slack, soff.as<uint32_t>(),
+                                cell.as<LocSegCell>(), pad, slack, place.as<int32_t>(),
+                                soff.as<uint32_t>(),
                                 lim.as<double2>(), nullptr, 0u, s));
     LOC_TRY(scan_counts(soff.as<uint32_t>(), ns, kMaxBlocks, sum, subtmp.as<uint32_t>(), &total,
                         s));
@@ -1233,7 +1296,8 @@ hipError_t build_p2p(Grid &g, double pad, double slack, hipStream_t s) {
     LOC_TRY(launch_fill_u32(last, 0xffffffffu, 15, s));  // no segments
     LOC_TRY(launch_fill_u32(last + 15, 0x7f800000u, 1, s));  // rest = +inf
     LOC_TRY(launch_loc_sub_segs(g, cnt.as<uint32_t>(), list.as<int32_t>(), group.as<int2>(), ng,
-                                cell.as<LocSegCell>(), pad, slack, soff.as<uint32_t>(),
+                                cell.as<LocSegCell>(), pad, slack, place.as<int32_t>(),
+                                soff.as<uint32_t>(),
                                 lim.as<double2>(), block.as<LocBlock>(), (uint32_t)total, s));
   }
   LOC_TRY(hipStreamSynchronize(s));
