@@ -574,7 +574,6 @@ extern "C" void gp_grid_free(gp_grid *g) {
   (void)hipFree(g->d_loc_cell);
   (void)hipFree(g->d_loc_sub);
   (void)hipFree(g->d_loc_slot);
-  (void)hipFree(g->d_loc_soff);
   (void)hipFree(g->d_loc_seg);
   (void)hipFree(g->d_loc_scell);
   (void)hipFree(g->d_loc_block);

@@ -96,8 +96,10 @@ struct LocCell {
 // its reach), a block of a subcell's list (entries with endpoints a and b, x | y << 16 in
 // steps of the cell's frame, and the segment, -1 where the last block has none; rest, a lower
 // bound in steps for the later entries' distance to the subcell's centre, +inf in the last
-// block) and a segment by value with its polyline.  An empty list is one block without segments.
-constexpr int LOC_ENTRIES = 5;
+// block) and a segment by value with its polyline.  A list begins with the two blocks of its
+// subcell's line, of LOC_LINE entries; the last place of the second holds, in a, the index of
+// the block that goes on.
+constexpr int LOC_ENTRIES = 5, LOC_LINE = 9;
 struct alignas(16) LocSegCell {
   uint32_t base, m;
   double reach;
@@ -150,9 +152,9 @@ struct Grid {
   LocCell *d_loc_cell;     // the locator (gp_locate.hip), null when the grid has none
   int32_t *d_loc_sub;     // PIP
   double4 *d_loc_slot;
-  uint32_t *d_loc_soff;   // P2P
-  LocSegCell *d_loc_scell;
+  LocSegCell *d_loc_scell;  // P2P
   LocBlock *d_loc_block;
+  uint32_t loc_lines;
   LocSeg *d_loc_seg;
   int64_t loc_bytes;
   gp_tuning tune[2];
@@ -168,8 +170,8 @@ struct LocArgs {
   const int32_t *sub;       //   answer (>= -1) or -(first slot + 2)
   const double4 *slot;      //   lists: per polygon a header and its elements
   const LocSegCell *scell;  // P2P: [ncells]
-  const uint32_t *soff;     //   first block of each subcell
-  const LocBlock *block;
+  const LocBlock *block;    //   the subcells' lines, then the further blocks
+  uint32_t lines;           //   blocks of the lines: 2 per subcell
   const LocSeg *lseg;       //   [nseg]
   double D2_next;           // the smallest double above fl(D*D)
 };

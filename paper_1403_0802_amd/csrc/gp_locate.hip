@@ -578,6 +578,12 @@ __global__ void k_loc_segments(const uint32_t *order, const int32_t *f, const do
   }
 }
 
+__global__ void k_loc_add(uint32_t *v, size_t n, uint32_t d) {
+  for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n;
+       i += (size_t)gridDim.x * blockDim.x)
+    v[i] += d;
+}
+
 // Frame of a cell's entries: the cell widened by its reach on every side, in LOC_UNITS
 // steps.  An entry is the part of its segment inside the frame, endpoints rounded to whole
 // steps: for a point of the cell that distance is within 0.71 steps of the segment's
@@ -616,10 +622,10 @@ __device__ __forceinline__ uint2 quantised(const double4 e, double ox, double oy
 // group (by the same rule, with the group's box) are dropped; the rest are broadcast
 // through LDS.  A list is ordered by rings around the subcell's centre, LOC_RINGS of equal
 // width from its nearest segment to its limit, so that a query can stop at the first block
-// whose rings are too far.
-// EMIT = false: blocks per subcell in cnt, the distance of the nearest segment and the
-// squared limit in lim; EMIT: cnt holds the first blocks, and receives `empty`, the block
-// that all empty lists share, where there are none.
+// whose rings are too far.  The first blocks of subcell s are 2 s and 2 s + 1, one 128-byte
+// line; the second gives up an entry for the index of the block that goes on.
+// EMIT = false: blocks beyond the line per subcell in cnt, the distance of the nearest
+// segment and the squared limit in lim; EMIT: cnt holds the first of those blocks.
 constexpr int LOC_RINGS = 8;
 
 template <bool EMIT>
@@ -627,7 +633,7 @@ __global__ __launch_bounds__(256) void k_loc_sub_segs(
     const uint32_t *first, const int32_t *list, const double4 *edge64, const int2 *group,
     uint32_t ngroups, const LocSegCell *cell, double x0, double y0, double cs, int32_t nx,
     double pad, double D, double slack, const int32_t *place, uint32_t *cnt, double2 *lim,
-    LocBlock *block, uint32_t empty) {
+    LocBlock *block) {
   __shared__ double4 sa[256 / GP_WAVE][GP_WAVE];  // a.x, a.y, d.x, d.y
   __shared__ double si[256 / GP_WAVE][GP_WAVE];   // 1 / |d|^2
   __shared__ uint2 sl[256 / GP_WAVE][GP_WAVE];    // the entry
@@ -700,7 +706,7 @@ __global__ __launch_bounds__(256) void k_loc_sub_segs(
     uint32_t n = 0;
     sweep([&](int, double d2) { n += !(d2 > lim2); });
     if (g.act) {
-      cnt[at] = (n + LOC_ENTRIES - 1) / LOC_ENTRIES;
+      cnt[at] = n > LOC_LINE ? (n - LOC_LINE + LOC_ENTRIES - 1) / LOC_ENTRIES : 0u;
       lim[at] = make_double2(sqrt(dmin), lim2);
     }
   } else {
@@ -726,32 +732,43 @@ __global__ __launch_bounds__(256) void k_loc_sub_segs(
     });
 #pragma unroll
     for (int i = 1; i <= LOC_RINGS; ++i) ring[i][tid] += ring[i - 1][tid];
-    const uint32_t n = ring[LOC_RINGS][tid], nb = (n + LOC_ENTRIES - 1) / LOC_ENTRIES;
-    LocBlock *out = g.act ? block + cnt[at] : nullptr;
-    if (g.act && n == 0) cnt[at] = empty;
+    const uint32_t n = ring[LOC_RINGS][tid];
+    const uint32_t more = g.act ? cnt[at] : 0u;
+    // block and slot of entry e
+    auto block_of = [&](uint32_t e) {
+      return e < LOC_LINE ? 2 * at + e / LOC_ENTRIES : more + (e - LOC_LINE) / LOC_ENTRIES;
+    };
+    auto slot_of = [](uint32_t e) { return (e < LOC_LINE ? e : e - LOC_LINE) % LOC_ENTRIES; };
     if (g.act) {
       // a block's `rest` is at most the distance to the centre of any later entry, in steps
       // of the frame; the last block's ends the list
       const double f = LOC_UNITS / (cs + 2.0 * ce.reach) * (1.0 - 0x1p-16);
-      for (uint32_t k = 0; k < nb; ++k) {
-        const uint32_t e = (k + 1) * LOC_ENTRIES;
+      auto rest = [&](uint32_t e) {  // of the block before the one entry e begins
         int i = 0;
         while (i + 1 < LOC_RINGS && ring[i + 1][tid] <= e) ++i;
-        out[k].rest = e < n ? (float)((dl.x + (double)i * step) * f) : INFINITY;
-      }
-      for (uint32_t e = n; e < nb * LOC_ENTRIES; ++e) {
-        LocBlock &o = out[e / LOC_ENTRIES];
-        o.a[e % LOC_ENTRIES] = o.b[e % LOC_ENTRIES] = 0u;
-        o.seg[e % LOC_ENTRIES] = -1;
+        return e < n ? (float)((dl.x + (double)i * step) * f) : INFINITY;
+      };
+      block[2 * at].rest = rest(LOC_ENTRIES);
+      LocBlock &l = block[2 * at + 1];
+      l.rest = rest(LOC_LINE);
+      l.a[LOC_ENTRIES - 1] = more;
+      l.b[LOC_ENTRIES - 1] = 0u;
+      l.seg[LOC_ENTRIES - 1] = -1;
+      uint32_t e = LOC_LINE;
+      for (; e < n; e += LOC_ENTRIES) block[block_of(e)].rest = rest(e + LOC_ENTRIES);
+      for (uint32_t k = n; k < e; ++k) {  // places without an entry
+        LocBlock &o = block[block_of(k)];
+        o.a[slot_of(k)] = o.b[slot_of(k)] = 0u;
+        o.seg[slot_of(k)] = -1;
       }
     }
     sweep([&](int q, double d2) {
       if (g.act && !(d2 > lim2)) {
         const uint32_t e = ring[ring_of(d2)][tid]++;
-        LocBlock &o = out[e / LOC_ENTRIES];
-        o.a[e % LOC_ENTRIES] = sl[wave][q].x;
-        o.b[e % LOC_ENTRIES] = sl[wave][q].y;
-        o.seg[e % LOC_ENTRIES] = sg[wave][q];
+        LocBlock &o = block[block_of(e)];
+        o.a[slot_of(e)] = sl[wave][q].x;
+        o.b[slot_of(e)] = sl[wave][q].y;
+        o.seg[slot_of(e)] = sg[wave][q];
       }
     });
   }
@@ -859,87 +876,137 @@ __device__ __forceinline__ float entry_d2(float px, float py, uint32_t a, uint32
   return fmaf(ex, ex, ey * ey);
 }
 
+// The 64-byte records idx of the lanes that have one (LOC_NONE: none), each into its lane's
+// w.  A lane's own four loads of a line would go to the cache one after another, the later
+// ones waiting on the first one's miss; instead the four lanes of a quad load one record
+// together, a record after the other, straight into LDS (lane l of load i to unit
+// 64 i + l), and each lane reads its record back.  Chunk c of a record lies at position
+// (c + quad) mod 4 of its four units, which leaves two lanes to a bank at most.
+// Called by whole waves.
+constexpr uint32_t LOC_NONE = 0xffffffffu;
+
+template <int I>
+__device__ __forceinline__ uint32_t quad_lane(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, I * 0x55, 0xf, 0xf, true);
+}
+
+__device__ __forceinline__ void fetch64(const void *base, uint32_t idx, uint4 *lds, uint4 (&w)[4]) {
+  const uint32_t lane = lane_id(), quad = lane >> 2;
+  const char *chunk = (const char *)base + (((lane - quad) & 3u) << 4);
+  auto load = [&](uint32_t i, uint32_t o) {
+    if (o != LOC_NONE)
+      __builtin_amdgcn_global_load_lds(
+          (const __attribute__((address_space(1))) void *)(chunk + ((uint64_t)o << 6)),
+          (__attribute__((address_space(3))) void *)(lds + GP_WAVE * i), 16, 0, 0);
+  };
+  load(0, quad_lane<0>(idx));
+  load(1, quad_lane<1>(idx));
+  load(2, quad_lane<2>(idx));
+  load(3, quad_lane<3>(idx));
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  wave_lds_sync();
+  const uint4 *mine = lds + GP_WAVE * (lane & 3u) + (lane & ~3u);
+#pragma unroll
+  for (uint32_t c = 0; c < 4; ++c) w[c] = mine[(c + quad) & 3u];
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // read before the next records land
+}
+
 // One point per lane: the FP32 distances of its subcell's entries keep the two nearest (and
 // the third's distance); the entries within twice the error of the nearest, one as a rule,
 // are decided by their exact distances (smaller distance, then smaller polyline).  Bound by
-// the gathers of the lists (200M points: 5.4 L2 lines missed and 27 requested a point).
-// Road map of 5.3M vertices: 200M points 167 -> 31.8 ms against the tiled refinement, 20M
-// with segment lists 5.98 -> 3.39 ms, 1,500 points 0.58 -> 0.012 ms.
+// the gathers of lists and segments.
+// Road map of 5.3M vertices: 200M points 167 -> 8.7 ms against the tiled refinement, 20M
+// with segment lists 5.91 -> 0.89 ms, 1,500 points 0.58 -> 0.009 ms; with each lane loading
+// its own records and an offset read ahead of them 13.2, 1.34 and 0.008 ms.
 __global__ __launch_bounds__(256) void k_locate_p2p(LocArgs a, const double *px,
                                                     const double *py, int64_t n,
                                                     int32_t *out_id, double *out_dist,
                                                     unsigned long long *counts) {
+  __shared__ uint4 stage[256 / GP_WAVE][4 * GP_WAVE];
   reset_counts(counts);
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x) {
-    const double x = px[i], y = py[i];
-    double ux, uy;
-    const int32_t c = locate_cell(a, x, y, ux, uy);
-    double best = a.D2_next;  // accept d2 <= fl(D*D); later only strictly smaller
-    int32_t id = -1;
-    if (c >= 0) {
-      const LocSegCell ce = a.scell[c];
-      if (ce.m != LOC_CONST) {
-        const double f = LOC_UNITS / (a.cs + 2.0 * ce.reach);
-        const float qx = (float)((ux * a.cs + ce.reach) * f);
-        const float qy = (float)((uy * a.cs + ce.reach) * f);
-        // distance to the subcell's centre, in steps, and the error of an entry's distance
-        const double k = (double)(1u << ce.m);
-        const float vx = (float)(ux * k - floor(ux * k)) - 0.5f;
-        const float vy = (float)(uy * k - floor(uy * k)) - 0.5f;
-        const float off = __builtin_amdgcn_sqrtf(fmaf(vx, vx, vy * vy)) *
-                              (float)(a.cs * f / k * (1.0 + 0x1p-16)) + LOC_ERR;
-        float b1 = INFINITY, b2 = INFINITY, b3 = INFINITY;
-        int32_t i1 = -1, i2 = -1;
-        auto meet = [&](uint32_t ea, uint32_t eb, int32_t seg) {
-          const float d = seg < 0 ? INFINITY : entry_d2(qx, qy, ea, eb);
-          b3 = __builtin_amdgcn_fmed3f(d, b2, b3);
-          i2 = d < b1 ? i1 : d < b2 ? seg : i2;
-          b2 = __builtin_amdgcn_fmed3f(d, b1, b2);
-          i1 = d < b1 ? seg : i1;
-          b1 = fminf(b1, d);
-        };
-        const uint32_t j0 = a.soff[subcell(ce.base, ce.m, ux, uy)];
-        // no later entry can be the nearest once its distance to the centre exceeds the
-        // point's and the nearest entry's together
-        auto enough = [&](float rest) {
-          return rest > off + __builtin_amdgcn_sqrtf(b1) * (1.0f + 0x1p-20f);
-        };
-        for (const LocBlock *q = a.block + j0;; ++q) {
-          const uint4 w0 = ((const uint4 *)q)[0], w1 = ((const uint4 *)q)[1],
-                      w2 = ((const uint4 *)q)[2], w3 = ((const uint4 *)q)[3];
-          meet(w0.x, w1.y, (int32_t)w2.z);
-          meet(w0.y, w1.z, (int32_t)w2.w);
-          meet(w0.z, w1.w, (int32_t)w3.x);
-          meet(w0.w, w2.x, (int32_t)w3.y);
-          meet(w1.x, w2.y, (int32_t)w3.z);
-          const float rest = __uint_as_float(w3.w);
-          if (rest == INFINITY || enough(rest)) break;
-        }
-        auto take = [&](int32_t sg) {
-          const LocSeg *g = a.lseg + sg;
-          const double d2 = exact_d2(x, y, g->e, a.D2_next);
-          const int32_t fl = g->f;
-          if (d2 < best || (d2 == best && fl < id)) {
-            best = d2;
-            id = fl;
-          }
-        };
-        // the error holds for distances, and 2^-20 covers the squares' and roots' rounding
-        const float lim = (__builtin_amdgcn_sqrtf(b1) + 2.0f * LOC_ERR) * (1.0f + 0x1p-20f);
-        const float lim2 = lim * lim;
-        if (b3 <= lim2) {
-          for (const LocBlock *q = a.block + j0;; ++q) {
-            for (int t = 0; t < LOC_ENTRIES; ++t)
-              if (q->seg[t] >= 0 && entry_d2(qx, qy, q->a[t], q->b[t]) <= lim2) take(q->seg[t]);
-            if (q->rest == INFINITY || enough(q->rest)) break;
-          }
-        } else {
-          if (i1 >= 0) take(i1);
-          if (b2 <= lim2) take(i2);
-        }
-      }
+  uint4 *lds = stage[threadIdx.x / GP_WAVE];
+  const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  const bool live = i < n;
+  const double x = live ? px[i] : (double)INFINITY, y = live ? py[i] : 0.0;
+  double ux, uy;
+  const int32_t c = locate_cell(a, x, y, ux, uy);
+  LocSegCell ce{0u, LOC_CONST, 0.0};
+  if (c >= 0) ce = a.scell[c];
+  const bool some = ce.m != LOC_CONST;
+  const uint32_t q0 = some ? 2 * subcell(ce.base, ce.m, ux, uy) : LOC_NONE;
+  const double f = LOC_UNITS / (a.cs + 2.0 * ce.reach);
+  const float qx = (float)((ux * a.cs + ce.reach) * f);
+  const float qy = (float)((uy * a.cs + ce.reach) * f);
+  // distance to the subcell's centre, in steps, and the error of an entry's distance
+  const double k = some ? (double)(1u << ce.m) : 1.0;
+  const float vx = (float)(ux * k - floor(ux * k)) - 0.5f;
+  const float vy = (float)(uy * k - floor(uy * k)) - 0.5f;
+  const float off = __builtin_amdgcn_sqrtf(fmaf(vx, vx, vy * vy)) *
+                        (float)(a.cs * f / k * (1.0 + 0x1p-16)) + LOC_ERR;
+  float b1 = INFINITY, b2 = INFINITY, b3 = INFINITY;
+  int32_t i1 = -1, i2 = -1;
+  auto meet = [&](uint32_t ea, uint32_t eb, uint32_t seg) {
+    const float d = (int32_t)seg < 0 ? INFINITY : entry_d2(qx, qy, ea, eb);
+    b3 = __builtin_amdgcn_fmed3f(d, b2, b3);
+    i2 = d < b1 ? i1 : d < b2 ? (int32_t)seg : i2;
+    b2 = __builtin_amdgcn_fmed3f(d, b1, b2);
+    i1 = d < b1 ? (int32_t)seg : i1;
+    b1 = fminf(b1, d);
+  };
+  // the block after q, or LOC_NONE: the list ends, or no later entry can be the nearest
+  // because its distance to the centre exceeds the point's and the nearest entry's together
+  auto after = [&](uint32_t q, uint32_t next, float rest) {
+    if (rest == INFINITY || rest > off + __builtin_amdgcn_sqrtf(b1) * (1.0f + 0x1p-20f))
+      return LOC_NONE;
+    return q < a.lines && (q & 1u) ? next : q + 1u;
+  };
+  uint4 w[4];
+  for (uint32_t q = q0; ballot(q != LOC_NONE);) {
+    fetch64(a.block, q, lds, w);
+    if (q != LOC_NONE) {
+      meet(w[0].x, w[1].y, w[2].z);
+      meet(w[0].y, w[1].z, w[2].w);
+      meet(w[0].z, w[1].w, w[3].x);
+      meet(w[0].w, w[2].x, w[3].y);
+      meet(w[1].x, w[2].y, w[3].z);
+      q = after(q, w[1].x, __uint_as_float(w[3].w));
     }
+  }
+  double best = a.D2_next;  // accept d2 <= fl(D*D); later only strictly smaller
+  int32_t id = -1;
+  auto take = [&](const double4 e, int32_t fl) {
+    const double d2 = exact_d2(x, y, e, a.D2_next);
+    if (d2 < best || (d2 == best && fl < id)) {
+      best = d2;
+      id = fl;
+    }
+  };
+  // the error holds for distances, and 2^-20 covers the squares' and roots' rounding
+  const float lim = (__builtin_amdgcn_sqrtf(b1) + 2.0f * LOC_ERR) * (1.0f + 0x1p-20f);
+  const float lim2 = lim * lim;
+  const bool many = b3 <= lim2;
+  auto decide = [&](int32_t sg) {  // LOC_NONE for the lanes with nothing to decide
+    if (!ballot(sg >= 0)) return;
+    fetch64(a.lseg, (uint32_t)sg, lds, w);
+    if (sg >= 0)
+      take(make_double4(__hiloint2double((int)w[0].y, (int)w[0].x),
+                        __hiloint2double((int)w[0].w, (int)w[0].z),
+                        __hiloint2double((int)w[1].y, (int)w[1].x),
+                        __hiloint2double((int)w[1].w, (int)w[1].z)),
+           (int32_t)w[2].x);
+  };
+  decide(many ? -1 : i1);
+  decide(many || !(b2 <= lim2) ? -1 : i2);
+  if (many) {
+    for (uint32_t q = q0; q != LOC_NONE;) {
+      const LocBlock &b = a.block[q];
+      for (int t = 0; t < LOC_ENTRIES; ++t)
+        if (b.seg[t] >= 0 && entry_d2(qx, qy, b.a[t], b.b[t]) <= lim2)
+          take(a.lseg[b.seg[t]].e, a.lseg[b.seg[t]].f);
+      q = after(q, b.a[LOC_ENTRIES - 1], b.rest);
+    }
+  }
+  if (live) {
     out_id[i] = id;
     out_dist[i] = id >= 0 ? sqrt(best) : INFINITY;
   }
@@ -1064,6 +1131,10 @@ static hipError_t launch_loc_p2p_cells(const Grid &g, const uint32_t *first, con
          g.nx, g.ny, r, g.D, slack, target, cap, nsub, cell, cost);
 }
 
+static hipError_t launch_loc_add(uint32_t *v, size_t n, uint32_t d, hipStream_t s) {
+  LAUNCH(k_loc_add, blocks_for((int64_t)n, 256, 8192), 256, v, n, d);
+}
+
 static hipError_t launch_loc_seg_keys(const Grid &g, uint32_t *key, hipStream_t s) {
   LAUNCH(k_loc_seg_keys, blocks_for(g.nedges, 256, 8192), 256, g.d_edge64, g.nedges, g.x0, g.y0,
          g.cs, g.nx, g.ny, key);
@@ -1083,13 +1154,13 @@ static hipError_t launch_loc_sub_segs(const Grid &g, const uint32_t *first, cons
                                       const int2 *group, uint32_t ngroups,
                                       const LocSegCell *cell, double pad, double slack,
                                       const int32_t *place, uint32_t *cnt, double2 *lim, LocBlock *block,
-                                      uint32_t empty, hipStream_t s) {
+                                      hipStream_t s) {
   const unsigned b = (ngroups + 3) / 4;
   if (block)
     LAUNCH(k_loc_sub_segs<true>, b, 256, first, list, g.d_edge64, group, ngroups, cell, g.x0,
-           g.y0, g.cs, g.nx, pad, g.D, slack, place, cnt, lim, block, empty);
+           g.y0, g.cs, g.nx, pad, g.D, slack, place, cnt, lim, block);
   LAUNCH(k_loc_sub_segs<false>, b, 256, first, list, g.d_edge64, group, ngroups, cell, g.x0,
-         g.y0, g.cs, g.nx, pad, g.D, slack, place, cnt, lim, block, empty);
+         g.y0, g.cs, g.nx, pad, g.D, slack, place, cnt, lim, block);
 }
 
 hipError_t launch_locate_pip(const LocArgs &a, const double *px, const double *py, int64_t n,
@@ -1100,7 +1171,7 @@ hipError_t launch_locate_pip(const LocArgs &a, const double *px, const double *p
 hipError_t launch_locate_p2p(const LocArgs &a, const double *px, const double *py, int64_t n,
                              int32_t *out_id, double *out_dist, unsigned long long *counts,
                              hipStream_t s) {
-  LAUNCH(k_locate_p2p, blocks_for(n, 256, 1 << 24), 256, a, px, py, n, out_id, out_dist, counts);
+  LAUNCH(k_locate_p2p, (unsigned)((n + 255) / 256), 256, a, px, py, n, out_id, out_dist, counts);
 }
 
 hipError_t launch_locate_count(const LocArgs &a, const double *px, const double *py, int64_t n,
@@ -1115,11 +1186,12 @@ hipError_t launch_locate_count(const LocArgs &a, const double *px, const double 
 
 namespace {
 
-// Limits of the index: slots of 32 bytes (PIP), expected entries and blocks of 5 of them
-// (P2P), tests of the build, and entries per subcell beyond which the tiled refinement, which
+// Limits of the index: slots of 32 bytes (PIP), subcells of a 128-byte line each, expected
+// entries and further blocks (P2P), tests of the build, and entries per subcell beyond which the tiled refinement, which
 // reads a list once for 64 and more points, is the better reader of it.
 constexpr int64_t kMaxSlots = int64_t(1) << 27;     // 4 GiB
 constexpr int64_t kMaxEntries = int64_t(1) << 29;
+constexpr int64_t kMaxLines = int64_t(1) << 25;     // 4 GiB
 constexpr int64_t kMaxBlocks = int64_t(1) << 27;    // 8 GiB
 constexpr int64_t kMaxElems = int64_t(1) << 26;     // 2 GiB while building
 constexpr int64_t kMaxSubcells = int64_t(1) << 27;  // 512 MiB
@@ -1246,7 +1318,7 @@ hipError_t build_p2p(Grid &g, double pad, double slack, hipStream_t s) {
                                  5u, nsub.as<uint32_t>(), cell.as<LocSegCell>(),
                                  sum.as<unsigned long long>(), s));
     LOC_TRY(read_back(cost, sum.p, 32, s));
-    if (cost[0] <= (unsigned long long)kMaxSubcells &&
+    if (cost[0] <= (unsigned long long)kMaxLines &&
         cost[1] <= (unsigned long long)kMaxBuildTests &&
         cost[2] <= (unsigned long long)kMaxEntries)
       break;
@@ -1287,26 +1359,24 @@ hipError_t build_p2p(Grid &g, double pad, double slack, hipStream_t s) {
     LOC_TRY(launch_loc_sub_segs(g, cnt.as<uint32_t>(), list.as<int32_t>(), group.as<int2>(), ng,
                                 cell.as<LocSegCell>(), pad, slack, place.as<int32_t>(),
                                 soff.as<uint32_t>(),
-                                lim.as<double2>(), nullptr, 0u, s));
+                                lim.as<double2>(), nullptr, s));
     LOC_TRY(scan_counts(soff.as<uint32_t>(), ns, kMaxBlocks, sum, subtmp.as<uint32_t>(), &total,
                         s));
     LOC_NEED(total <= kMaxBlocks && LOC_ENTRIES * total <= kMaxMeanEntries * (int64_t)ns);
-    LOC_NEED(block.alloc((size_t)(total + 1) * sizeof(LocBlock)));
-    uint32_t *last = (uint32_t *)(block.as<LocBlock>() + total);
-    LOC_TRY(launch_fill_u32(last, 0xffffffffu, 15, s));  // no segments
-    LOC_TRY(launch_fill_u32(last + 15, 0x7f800000u, 1, s));  // rest = +inf
+    LOC_NEED(block.alloc((size_t)(2 * ns + total) * sizeof(LocBlock)));
+    LOC_TRY(launch_loc_add(soff.as<uint32_t>(), ns, 2 * (uint32_t)ns, s));
     LOC_TRY(launch_loc_sub_segs(g, cnt.as<uint32_t>(), list.as<int32_t>(), group.as<int2>(), ng,
                                 cell.as<LocSegCell>(), pad, slack, place.as<int32_t>(),
                                 soff.as<uint32_t>(),
-                                lim.as<double2>(), block.as<LocBlock>(), (uint32_t)total, s));
+                                lim.as<double2>(), block.as<LocBlock>(), s));
   }
   LOC_TRY(hipStreamSynchronize(s));
   g.d_loc_scell = cell.take<LocSegCell>();
-  g.d_loc_soff = soff.take<uint32_t>();
   g.d_loc_block = block.take<LocBlock>();
+  g.loc_lines = 2 * (uint32_t)ns;
   g.d_loc_seg = seg.take<LocSeg>();
-  g.loc_bytes = (int64_t)(nc * sizeof(LocSegCell) + (ns + 1) * 4 + nseg * sizeof(LocSeg)) +
-                (total + 1) * (int64_t)sizeof(LocBlock);
+  g.loc_bytes = (int64_t)(nc * sizeof(LocSegCell) + nseg * sizeof(LocSeg)) +
+                (2 * (int64_t)ns + total) * (int64_t)sizeof(LocBlock);
   return hipSuccess;
 }
 
@@ -1332,9 +1402,9 @@ LocArgs locator_args(const Grid &g) {
   a.cell = g.d_loc_cell;
   a.sub = g.d_loc_sub;
   a.slot = g.d_loc_slot;
-  a.soff = g.d_loc_soff;
   a.scell = g.d_loc_scell;
   a.block = g.d_loc_block;
+  a.lines = g.loc_lines;
   a.lseg = g.d_loc_seg;
   a.D2_next = nextafter(g.D2, INFINITY);
   return a;
