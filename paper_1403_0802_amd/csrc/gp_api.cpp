@@ -374,10 +374,8 @@ extern "C" gp_status gp_build_grid(gp_kind kind, const gp_geometry *geom,
     GP_TRY_HIP_G(hipMalloc(&g->d_cand_off, ((size_t)ncells + 1) * 4));
     GP_TRY_HIP_G(hipMalloc(&g->d_cand_id, np * 4));
     GP_TRY_HIP_G(hipMalloc(&g->d_cell_edges, std::max<size_t>(ncells, 1) * 8));
-    GP_TRY_HIP_G(launch_fill_u32((uint32_t *)g->d_cand_off, 0u, (size_t)ncells + 1, s));
-    GP_TRY_HIP_G(launch_histogram(skeys, npairs, (uint32_t *)g->d_cand_off, s));
-    GP_TRY_HIP_G(launch_exclusive_scan_u32((uint32_t *)g->d_cand_off, (uint32_t *)g->d_cand_off,
-                                           (size_t)ncells + 1, stmp.as<uint32_t>(), s));
+    // the pairs are sorted by cell: a search per cell instead of an atomic per pair
+    GP_TRY_HIP_G(launch_offsets(skeys, npairs, ncells, g->d_cand_off, s));
     if (npairs)
       GP_TRY_HIP_G(hipMemcpyAsync(g->d_cand_id, svals, (size_t)npairs * 4,
                                   hipMemcpyDeviceToDevice, s));
@@ -509,10 +507,7 @@ extern "C" gp_status gp_build_grid(gp_kind kind, const gp_geometry *geom,
     GP_TRY_HIP_G(hipMalloc(&g->d_cseg, n2 * 4));
     GP_TRY_HIP_G(hipMalloc(&g->d_seg2f, (size_t)ns * 4));
     GP_TRY_HIP_G(hipMalloc(&g->d_cell_segs, std::max<size_t>(ncells, 1) * 8));
-    GP_TRY_HIP_G(launch_fill_u32((uint32_t *)g->d_cseg_off, 0u, (size_t)ncells + 1, s));
-    GP_TRY_HIP_G(launch_histogram(skeys, np2, (uint32_t *)g->d_cseg_off, s));
-    GP_TRY_HIP_G(launch_exclusive_scan_u32((uint32_t *)g->d_cseg_off, (uint32_t *)g->d_cseg_off,
-                                           (size_t)ncells + 1, stmp.as<uint32_t>(), s));
+    GP_TRY_HIP_G(launch_offsets(skeys, np2, ncells, g->d_cseg_off, s));
     if (np2)
       GP_TRY_HIP_G(hipMemcpyAsync(g->d_cseg, svals, (size_t)np2 * 4, hipMemcpyDeviceToDevice, s));
     GP_TRY_HIP_G(launch_seg2f(g->d_eoff, (int32_t)nf, g->d_seg2f, s));

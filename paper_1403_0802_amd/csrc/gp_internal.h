@@ -245,7 +245,6 @@ hipError_t launch_sum_u32(const uint32_t *v, size_t n, unsigned long long *out, 
 hipError_t launch_raster_emit(const double *mbb, int32_t nf, double x0, double y0, double cs,
                               int32_t nx, int32_t ny, const uint32_t *off, uint32_t *pair_cell,
                               uint32_t *pair_fid, hipStream_t s);
-hipError_t launch_histogram(const uint32_t *keys, size_t n, uint32_t *cnt, hipStream_t s);
 hipError_t launch_cell_edges(const int32_t *cand_off, const int32_t *cand_id,
                              const int32_t *eoff, const uint8_t *cand_class, int32_t ncells,
                              int64_t *cell_edges, hipStream_t s);

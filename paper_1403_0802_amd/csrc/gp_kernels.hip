@@ -568,29 +568,40 @@ hipError_t launch_cell_counts(const int32_t *off, int32_t ncells, int64_t *cnt, 
   return hipGetLastError();
 }
 
-// Feature MBB over all of its vertices; P2P expands by D; both pad by cs*2^-20.
-__global__ void k_mbb(const int32_t *rvo, const int32_t *fro, const double *x, const double *y,
-                      int32_t nf, int kind, double D, double cs, double *mbb) {
+// Feature MBB over all of its vertices; P2P expands by D; both pad by cs*2^-20.  One wave per
+// feature: a thread per feature walks the longest polygon alone (50,000 vertices: 5.0 ms
+// against 0.05 ms).  Minima and maxima do not depend on the order.
+__global__ __launch_bounds__(256) void k_mbb(const int32_t *rvo, const int32_t *fro,
+                                             const double *x, const double *y, int32_t nf,
+                                             int kind, double D, double cs, double *mbb) {
   const double pad = cs * 0x1p-20;
-  for (int32_t f = blockIdx.x * blockDim.x + threadIdx.x; f < nf;
-       f += gridDim.x * blockDim.x) {
-    int32_t v0 = kind == GP_PIP ? rvo[fro[f]] : rvo[f];
-    int32_t v1 = kind == GP_PIP ? rvo[fro[f + 1]] : rvo[f + 1];
+  const int32_t nw = (int32_t)(gridDim.x * (blockDim.x / GP_WAVE));
+  for (int32_t f = (int32_t)(blockIdx.x * (blockDim.x / GP_WAVE) + threadIdx.x / GP_WAVE); f < nf;
+       f += nw) {
+    const int32_t v0 = kind == GP_PIP ? rvo[fro[f]] : rvo[f];
+    const int32_t v1 = kind == GP_PIP ? rvo[fro[f + 1]] : rvo[f + 1];
     double mnx = INFINITY, mny = INFINITY, mxx = -INFINITY, mxy = -INFINITY;
-    for (int32_t v = v0; v < v1; ++v) {
-      double a = x[v], b = y[v];
-      if (a < mnx) mnx = a;
-      if (a > mxx) mxx = a;
-      if (b < mny) mny = b;
-      if (b > mxy) mxy = b;
+    for (int32_t v = v0 + (int32_t)lane_id(); v < v1; v += GP_WAVE) {
+      mnx = fmin(mnx, x[v]);
+      mxx = fmax(mxx, x[v]);
+      mny = fmin(mny, y[v]);
+      mxy = fmax(mxy, y[v]);
+    }
+    for (int off = 32; off > 0; off >>= 1) {
+      mnx = fmin(mnx, __shfl_xor(mnx, off, GP_WAVE));
+      mxx = fmax(mxx, __shfl_xor(mxx, off, GP_WAVE));
+      mny = fmin(mny, __shfl_xor(mny, off, GP_WAVE));
+      mxy = fmax(mxy, __shfl_xor(mxy, off, GP_WAVE));
     }
     if (kind == GP_P2P) {
       mnx = mnx - D; mny = mny - D; mxx = mxx + D; mxy = mxy + D;
     }
-    mbb[4 * (size_t)f + 0] = mnx - pad;
-    mbb[4 * (size_t)f + 1] = mny - pad;
-    mbb[4 * (size_t)f + 2] = mxx + pad;
-    mbb[4 * (size_t)f + 3] = mxy + pad;
+    if (lane_id() == 0) {
+      mbb[4 * (size_t)f + 0] = mnx - pad;
+      mbb[4 * (size_t)f + 1] = mny - pad;
+      mbb[4 * (size_t)f + 2] = mxx + pad;
+      mbb[4 * (size_t)f + 3] = mxy + pad;
+    }
   }
 }
 
@@ -598,7 +609,7 @@ hipError_t launch_mbb(const int32_t *rvo, const int32_t *fro, const double *x, c
                       int32_t nf, gp_kind kind, double D, double cs, double *mbb,
                       hipStream_t s) {
   if (nf == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_mbb, dim3(grid_for(nf, 64, 8192)), dim3(64), 0, s, rvo, fro, x, y, nf,
+  hipLaunchKernelGGL(k_mbb, dim3(grid_for(nf, 4, 16384)), dim3(256), 0, s, rvo, fro, x, y, nf,
                      (int)kind, D, cs, mbb);
   return hipGetLastError();
 }
@@ -777,18 +788,6 @@ hipError_t launch_raster_emit(const double *mbb, int32_t nf, double x0, double y
   if (nf == 0) return hipSuccess;
   hipLaunchKernelGGL(k_raster_emit, dim3(nf < 65536 ? nf : 65536), dim3(64), 0, s, mbb, nf, x0,
                      y0, cs, nx, ny, off, pcell, pfid);
-  return hipGetLastError();
-}
-
-__global__ void k_histogram(const uint32_t *keys, size_t n, uint32_t *cnt) {
-  for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n;
-       i += (size_t)gridDim.x * blockDim.x)
-    atomicAdd(&cnt[keys[i]], 1u);
-}
-
-hipError_t launch_histogram(const uint32_t *keys, size_t n, uint32_t *cnt, hipStream_t s) {
-  if (n == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_histogram, dim3(grid_for(n, 256, 8192)), dim3(256), 0, s, keys, n, cnt);
   return hipGetLastError();
 }
 

@@ -1211,8 +1211,18 @@ struct Buf {
     p = nullptr;
     return false;
   }
-  template <class T> T *as() const { return (T *)p; }
+  template <class T> T *as(size_t off = 0) const { return (T *)((char *)p + off); }
   template <class T> T *take() { T *q = (T *)p; p = nullptr; return q; }
+};
+
+// Places in one buffer: an allocation costs the build more than most of its kernels.
+struct Places {
+  size_t bytes = 0;
+  size_t add(size_t n) {
+    const size_t o = bytes;
+    bytes = (bytes + n + 255) / 256 * 256;
+    return o;
+  }
 };
 
 #define LOC_TRY(expr)                      \
@@ -1232,12 +1242,12 @@ hipError_t read_back(void *dst, const void *src, size_t bytes, hipStream_t s) {
 
 // cnt[0 .. n) becomes its exclusive prefix sum with the total at cnt[n]; *total in 64 bits
 // (nothing is scanned when it passes `most`).
-hipError_t scan_counts(uint32_t *cnt, size_t n, int64_t most, Buf &sum, uint32_t *tmp,
-                       int64_t *total, hipStream_t s) {
+hipError_t scan_counts(uint32_t *cnt, size_t n, int64_t most, unsigned long long *sum,
+                       uint32_t *tmp, int64_t *total, hipStream_t s) {
   unsigned long long t = 0;
   LOC_TRY(launch_fill_u32(cnt + n, 0u, 1, s));
-  LOC_TRY(launch_sum_u32(cnt, n, sum.as<unsigned long long>(), s));
-  LOC_TRY(read_back(&t, sum.p, 8, s));
+  LOC_TRY(launch_sum_u32(cnt, n, sum, s));
+  LOC_TRY(read_back(&t, sum, 8, s));
   *total = t > (unsigned long long)INT64_MAX ? INT64_MAX : (int64_t)t;
   if (*total > most) return hipSuccess;
   return launch_exclusive_scan_u32(cnt, cnt, n + 1, tmp, s);
@@ -1245,81 +1255,104 @@ hipError_t scan_counts(uint32_t *cnt, size_t n, int64_t most, Buf &sum, uint32_t
 
 hipError_t build_pip(Grid &g, const LocBuild &b, double pad, hipStream_t s) {
   const size_t np = (size_t)g.npairs, nc = (size_t)g.ncells;
-  Buf prev, cnt, par, elem, nsub, cell, sum, tmp, scnt, sub, slot, subtmp, group;
-  LOC_NEED(prev.alloc((size_t)g.nedges * 4) && cnt.alloc((np + 1) * 4) && par.alloc(np) &&
-           nsub.alloc((nc + 1) * 4) && cell.alloc(nc * sizeof(LocCell)) && sum.alloc(64) &&
-           tmp.alloc(scan_tmp_elems(std::max(np, nc) + 1) * 4));
+  Buf b1, b2, elems, cells, subs, slots;
+  Places p1;
+  const size_t o_prev = p1.add((size_t)g.nedges * 4), o_cnt = p1.add((np + 1) * 4),
+               o_par = p1.add(np), o_nsub = p1.add((nc + 1) * 4), o_sum = p1.add(64),
+               o_tmp = p1.add(scan_tmp_elems(std::max(np, nc) + 1) * 4);
+  LOC_NEED(b1.alloc(p1.bytes) && cells.alloc(nc * sizeof(LocCell)));
+  int32_t *prev = b1.as<int32_t>(o_prev);
+  uint32_t *cnt = b1.as<uint32_t>(o_cnt), *nsub = b1.as<uint32_t>(o_nsub),
+           *tmp = b1.as<uint32_t>(o_tmp);
+  uint8_t *par = b1.as<uint8_t>(o_par);
+  unsigned long long *sum = b1.as<unsigned long long>(o_sum);
+  LocCell *cell = cells.as<LocCell>();
   int64_t total = 0;
-  LOC_TRY(launch_loc_ring_prev(b.ring_off, b.n_rings, prev.as<int32_t>(), s));
-  if (np)
-    LOC_TRY(launch_loc_pip_pairs(g, b.pair_cell, b.vy, prev.as<int32_t>(), pad,
-                                 cnt.as<uint32_t>(), par.as<uint8_t>(), nullptr, s));
-  LOC_TRY(scan_counts(cnt.as<uint32_t>(), np, kMaxElems, sum, tmp.as<uint32_t>(), &total, s));
-  LOC_NEED(total <= kMaxElems && elem.alloc((size_t)total * 32));
-  if (total)
-    LOC_TRY(launch_loc_pip_pairs(g, b.pair_cell, b.vy, prev.as<int32_t>(), pad,
-                                 cnt.as<uint32_t>(), par.as<uint8_t>(), elem.as<double4>(), s));
+  LOC_TRY(launch_loc_ring_prev(b.ring_off, b.n_rings, prev, s));
+  if (np) LOC_TRY(launch_loc_pip_pairs(g, b.pair_cell, b.vy, prev, pad, cnt, par, nullptr, s));
+  LOC_TRY(scan_counts(cnt, np, kMaxElems, sum, tmp, &total, s));
+  LOC_NEED(total <= kMaxElems && elems.alloc((size_t)total * 32));
+  double4 *elem = elems.as<double4>();
+  if (total) LOC_TRY(launch_loc_pip_pairs(g, b.pair_cell, b.vy, prev, pad, cnt, par, elem, s));
   // the finest subdivision whose size and build stay within the limits
   unsigned long long cost[3] = {0, 0, 0};
   for (int cap = 6; cap >= 0; --cap) {
-    LOC_TRY(launch_fill_u32(sum.as<uint32_t>(), 0u, 6, s));
-    LOC_TRY(launch_loc_pip_cells(g, cnt.as<uint32_t>(), par.as<uint8_t>(), (uint32_t)cap,
-                                 nsub.as<uint32_t>(), cell.as<LocCell>(),
-                                 sum.as<unsigned long long>(), s));
-    LOC_TRY(read_back(cost, sum.p, 24, s));
+    LOC_TRY(launch_fill_u32((uint32_t *)sum, 0u, 6, s));
+    LOC_TRY(launch_loc_pip_cells(g, cnt, par, (uint32_t)cap, nsub, cell, sum, s));
+    LOC_TRY(read_back(cost, sum, 24, s));
     if (cost[0] <= (unsigned long long)kMaxSubcells && cost[1] <= (unsigned long long)kMaxBuildTests)
       break;
     LOC_NEED(cap > 0);
   }
   const size_t ns = (size_t)cost[0];
-  LOC_TRY(launch_exclusive_scan_u32(nsub.as<uint32_t>(), nsub.as<uint32_t>(), nc + 1,
-                                    tmp.as<uint32_t>(), s));
   const uint32_t ng = (uint32_t)cost[2];
-  LOC_NEED(group.alloc((size_t)ng * 8));
-  LOC_TRY(launch_loc_groups(g, nsub.as<uint32_t>(), cell.as<LocCell>(),
-                            sum.as<uint32_t>(), group.as<int2>(), s));
+  Places p2;
+  const size_t o_group = p2.add((size_t)ng * 8), o_scnt = p2.add((ns + 1) * 4),
+               o_stmp = p2.add(scan_tmp_elems(ns + 1) * 4);
+  LOC_NEED(b2.alloc(p2.bytes) && subs.alloc(ns * 4));
+  int2 *group = b2.as<int2>(o_group);
+  uint32_t *scnt = b2.as<uint32_t>(o_scnt);
+  LOC_TRY(launch_exclusive_scan_u32(nsub, nsub, nc + 1, tmp, s));
+  LOC_TRY(launch_loc_groups(g, nsub, cell, (uint32_t *)sum, group, s));
   total = 0;
-  LOC_NEED(sub.alloc(ns * 4) && scnt.alloc((ns + 1) * 4) &&
-           subtmp.alloc(scan_tmp_elems(ns + 1) * 4));
   if (ns) {
-    LOC_TRY(launch_loc_pip_sub(g, group.as<int2>(), ng, cnt.as<uint32_t>(), par.as<uint8_t>(),
-                               elem.as<double4>(), cell.as<LocCell>(), pad, scnt.as<uint32_t>(), nullptr, nullptr, s));
-    LOC_TRY(scan_counts(scnt.as<uint32_t>(), ns, kMaxSlots, sum, subtmp.as<uint32_t>(), &total, s));
+    LOC_TRY(launch_loc_pip_sub(g, group, ng, cnt, par, elem, cell, pad, scnt, nullptr, nullptr, s));
+    LOC_TRY(scan_counts(scnt, ns, kMaxSlots, sum, b2.as<uint32_t>(o_stmp), &total, s));
     LOC_NEED(total <= kMaxSlots && total <= kMaxMeanEntries * (int64_t)ns);
-    LOC_NEED(slot.alloc((size_t)total * 32));
-    LOC_TRY(launch_loc_pip_sub(g, group.as<int2>(), ng, cnt.as<uint32_t>(), par.as<uint8_t>(),
-                               elem.as<double4>(), cell.as<LocCell>(), pad, scnt.as<uint32_t>(), slot.as<double4>(),
-                               sub.as<int32_t>(), s));
+    LOC_NEED(slots.alloc((size_t)total * 32));
+    LOC_TRY(launch_loc_pip_sub(g, group, ng, cnt, par, elem, cell, pad, scnt, slots.as<double4>(),
+                               subs.as<int32_t>(), s));
   }
   LOC_TRY(hipStreamSynchronize(s));  // before the temporaries go
-  g.d_loc_cell = cell.take<LocCell>();
-  g.d_loc_sub = sub.take<int32_t>();
-  g.d_loc_slot = slot.take<double4>();
+  g.d_loc_cell = cells.take<LocCell>();
+  g.d_loc_sub = subs.take<int32_t>();
+  g.d_loc_slot = slots.take<double4>();
   g.loc_bytes = (int64_t)(nc * sizeof(LocCell) + ns * 4) + total * 32;
   return hipSuccess;
 }
 
 hipError_t build_p2p(Grid &g, double pad, double slack, hipStream_t s) {
   const size_t nc = (size_t)g.ncells, nseg = (size_t)g.nedges;
-  Buf cnt, cmin, list, nsub, cell, sum, tmp, soff, block, seg, subtmp, group, lim, place;
-  LOC_NEED(cnt.alloc((nc + 1) * 4) && cmin.alloc(nc * 8) && nsub.alloc((nc + 1) * 4) &&
-           cell.alloc(nc * sizeof(LocSegCell)) && sum.alloc(64) &&
-           tmp.alloc(scan_tmp_elems(nc + 1) * 4));
+  Buf b1, b2, lists, cells, blocks, segs;
+  Places p1;
+  const size_t o_cnt = p1.add((nc + 1) * 4), o_cmin = p1.add(nc * 8),
+               o_nsub = p1.add((nc + 1) * 4), o_sum = p1.add(64),
+               o_tmp = p1.add(scan_tmp_elems(std::max(nc + 1, radix_hist_elems(nseg))) * 4),
+               o_kA = p1.add(nseg * 4), o_kB = p1.add(nseg * 4), o_vA = p1.add(nseg * 4),
+               o_vB = p1.add(nseg * 4), o_poly = p1.add(nseg * 4),
+               o_hist = p1.add(radix_hist_elems(nseg) * 4), o_place = p1.add(nseg * 4);
+  LOC_NEED(b1.alloc(p1.bytes) && cells.alloc(nc * sizeof(LocSegCell)) &&
+           segs.alloc(nseg * sizeof(LocSeg)));
+  uint32_t *cnt = b1.as<uint32_t>(o_cnt), *nsub = b1.as<uint32_t>(o_nsub),
+           *tmp = b1.as<uint32_t>(o_tmp);
+  double *cmin = b1.as<double>(o_cmin);
+  unsigned long long *sum = b1.as<unsigned long long>(o_sum);
+  int32_t *place = b1.as<int32_t>(o_place);
+  LocSegCell *cell = cells.as<LocSegCell>();
+  if (nseg) {  // the segments in the order of the cells
+    uint32_t *keys = nullptr, *order = nullptr;
+    int bits = 1;
+    while (bits < 31 && (1 << bits) < g.ncells) ++bits;
+    LOC_TRY(launch_loc_seg_keys(g, b1.as<uint32_t>(o_kA), s));
+    LOC_TRY(launch_loc_polylines(g, b1.as<int32_t>(o_poly), s));
+    LOC_TRY(launch_radix_sort(b1.as<uint32_t>(o_kA), b1.as<uint32_t>(o_kB),
+                              b1.as<uint32_t>(o_vA), b1.as<uint32_t>(o_vB), nseg, bits, true,
+                              b1.as<uint32_t>(o_hist), tmp, s, &keys, &order));
+    LOC_TRY(launch_loc_segments(g, order, b1.as<int32_t>(o_poly), segs.as<LocSeg>(), place, s));
+  }
+  // the cells' segments
   const double r = 0.70710678118654757 * (1.0 + 0x1p-40) * (g.cs + 2.0 * pad);
   int64_t total = 0;
-  LOC_TRY(launch_loc_cell_segs(g, r, slack, cnt.as<uint32_t>(), cmin.as<double>(), nullptr, s));
-  LOC_TRY(scan_counts(cnt.as<uint32_t>(), nc, kMaxEntries, sum, tmp.as<uint32_t>(), &total, s));
-  LOC_NEED(total <= kMaxEntries && list.alloc((size_t)total * 4));
-  if (total)
-    LOC_TRY(launch_loc_cell_segs(g, r, slack, cnt.as<uint32_t>(), cmin.as<double>(),
-                                 list.as<int32_t>(), s));
+  LOC_TRY(launch_loc_cell_segs(g, r, slack, cnt, cmin, nullptr, s));
+  LOC_TRY(scan_counts(cnt, nc, kMaxEntries, sum, tmp, &total, s));
+  LOC_NEED(total <= kMaxEntries && lists.alloc((size_t)total * 4));
+  int32_t *list = lists.as<int32_t>();
+  if (total) LOC_TRY(launch_loc_cell_segs(g, r, slack, cnt, cmin, list, s));
   unsigned long long cost[4] = {0, 0, 0, 0};
   for (uint32_t target = kLocTarget;; target *= 2) {
-    LOC_TRY(launch_fill_u32(sum.as<uint32_t>(), 0u, 8, s));
-    LOC_TRY(launch_loc_p2p_cells(g, cnt.as<uint32_t>(), cmin.as<double>(), r, slack + pad, target,
-                                 5u, nsub.as<uint32_t>(), cell.as<LocSegCell>(),
-                                 sum.as<unsigned long long>(), s));
-    LOC_TRY(read_back(cost, sum.p, 32, s));
+    LOC_TRY(launch_fill_u32((uint32_t *)sum, 0u, 8, s));
+    LOC_TRY(launch_loc_p2p_cells(g, cnt, cmin, r, slack + pad, target, 5u, nsub, cell, sum, s));
+    LOC_TRY(read_back(cost, sum, 32, s));
     if (cost[0] <= (unsigned long long)kMaxLines &&
         cost[1] <= (unsigned long long)kMaxBuildTests &&
         cost[2] <= (unsigned long long)kMaxEntries)
@@ -1327,56 +1360,32 @@ hipError_t build_p2p(Grid &g, double pad, double slack, hipStream_t s) {
     LOC_NEED(target < (1u << 30));
   }
   const size_t ns = (size_t)cost[0];
-  LOC_TRY(launch_exclusive_scan_u32(nsub.as<uint32_t>(), nsub.as<uint32_t>(), nc + 1,
-                                    tmp.as<uint32_t>(), s));
   const uint32_t ng = (uint32_t)cost[3];
-  LOC_NEED(group.alloc((size_t)ng * 8) && lim.alloc(ns * 16));
-  LOC_TRY(launch_loc_groups(g, nsub.as<uint32_t>(), cell.as<LocSegCell>(),
-                            sum.as<uint32_t>(), group.as<int2>(), s));
+  Places p2;
+  const size_t o_group = p2.add((size_t)ng * 8), o_lim = p2.add(ns * 16),
+               o_soff = p2.add((ns + 1) * 4), o_stmp = p2.add(scan_tmp_elems(ns + 1) * 4);
+  LOC_NEED(b2.alloc(p2.bytes));
+  int2 *group = b2.as<int2>(o_group);
+  double2 *lim = b2.as<double2>(o_lim);
+  uint32_t *soff = b2.as<uint32_t>(o_soff);
+  LOC_TRY(launch_exclusive_scan_u32(nsub, nsub, nc + 1, tmp, s));
+  LOC_TRY(launch_loc_groups(g, nsub, cell, (uint32_t *)sum, group, s));
   total = 0;
-  LOC_NEED(soff.alloc((ns + 1) * 4) && subtmp.alloc(scan_tmp_elems(ns + 1) * 4) &&
-           seg.alloc(nseg * sizeof(LocSeg)));
-  LOC_NEED(place.alloc(nseg * 4));
-  {
-    Buf kA, kB, vA, vB, hist, htmp, poly;
-    LOC_NEED(kA.alloc(nseg * 4) && kB.alloc(nseg * 4) && vA.alloc(nseg * 4) &&
-             vB.alloc(nseg * 4) && poly.alloc(nseg * 4) &&
-             hist.alloc(radix_hist_elems(nseg) * 4) &&
-             htmp.alloc(scan_tmp_elems(radix_hist_elems(nseg)) * 4));
-    uint32_t *keys = nullptr, *order = nullptr;
-    int bits = 1;
-    while (bits < 31 && (1 << bits) < g.ncells) ++bits;
-    if (nseg) {
-      LOC_TRY(launch_loc_seg_keys(g, kA.as<uint32_t>(), s));
-      LOC_TRY(launch_loc_polylines(g, poly.as<int32_t>(), s));
-      LOC_TRY(launch_radix_sort(kA.as<uint32_t>(), kB.as<uint32_t>(), vA.as<uint32_t>(),
-                                vB.as<uint32_t>(), nseg, bits, true, hist.as<uint32_t>(),
-                                htmp.as<uint32_t>(), s, &keys, &order));
-      LOC_TRY(launch_loc_segments(g, order, poly.as<int32_t>(), seg.as<LocSeg>(),
-                                  place.as<int32_t>(), s));
-    }
-    LOC_TRY(hipStreamSynchronize(s));  // before the sort's buffers go
-  }
   if (ns) {
-    LOC_TRY(launch_loc_sub_segs(g, cnt.as<uint32_t>(), list.as<int32_t>(), group.as<int2>(), ng,
-                                cell.as<LocSegCell>(), pad, slack, place.as<int32_t>(),
-                                soff.as<uint32_t>(),
-                                lim.as<double2>(), nullptr, s));
-    LOC_TRY(scan_counts(soff.as<uint32_t>(), ns, kMaxBlocks, sum, subtmp.as<uint32_t>(), &total,
-                        s));
+    LOC_TRY(launch_loc_sub_segs(g, cnt, list, group, ng, cell, pad, slack, place, soff, lim,
+                                nullptr, s));
+    LOC_TRY(scan_counts(soff, ns, kMaxBlocks, sum, b2.as<uint32_t>(o_stmp), &total, s));
     LOC_NEED(total <= kMaxBlocks && LOC_ENTRIES * total <= kMaxMeanEntries * (int64_t)ns);
-    LOC_NEED(block.alloc((size_t)(2 * ns + total) * sizeof(LocBlock)));
-    LOC_TRY(launch_loc_add(soff.as<uint32_t>(), ns, 2 * (uint32_t)ns, s));
-    LOC_TRY(launch_loc_sub_segs(g, cnt.as<uint32_t>(), list.as<int32_t>(), group.as<int2>(), ng,
-                                cell.as<LocSegCell>(), pad, slack, place.as<int32_t>(),
-                                soff.as<uint32_t>(),
-                                lim.as<double2>(), block.as<LocBlock>(), s));
+    LOC_NEED(blocks.alloc((size_t)(2 * ns + total) * sizeof(LocBlock)));
+    LOC_TRY(launch_loc_add(soff, ns, 2 * (uint32_t)ns, s));
+    LOC_TRY(launch_loc_sub_segs(g, cnt, list, group, ng, cell, pad, slack, place, soff, lim,
+                                blocks.as<LocBlock>(), s));
   }
   LOC_TRY(hipStreamSynchronize(s));
-  g.d_loc_scell = cell.take<LocSegCell>();
-  g.d_loc_block = block.take<LocBlock>();
+  g.d_loc_scell = cells.take<LocSegCell>();
+  g.d_loc_block = blocks.take<LocBlock>();
   g.loc_lines = 2 * (uint32_t)ns;
-  g.d_loc_seg = seg.take<LocSeg>();
+  g.d_loc_seg = segs.take<LocSeg>();
   g.loc_bytes = (int64_t)(nc * sizeof(LocSegCell) + nseg * sizeof(LocSeg)) +
                 (2 * (int64_t)ns + total) * (int64_t)sizeof(LocBlock);
   return hipSuccess;
