@@ -705,6 +705,10 @@ bool uses_locator(const Grid &g, gp_precision prec) {
   return (g.d_loc_cell || g.d_loc_scell) && !g.tune_explicit[prec];
 }
 
+const int64_t *counted_tests(const Grid &g, gp_precision prec) {
+  return prec == GP_MIXED && g.d_cseg_off ? g.d_cell_segs : g.d_cell_edges;
+}
+
 // The query on the locator; both precision forms, whose results are the same bits.
 // `count` leaves the test counters in the workspace (stats implies it).
 static gp_status run_locator(const gp_grid *g, int64_t n, const double *px, const double *py,
@@ -718,14 +722,13 @@ static gp_status run_locator(const gp_grid *g, int64_t n, const double *px, cons
     GP_TRY_HIP(hipEventRecord(ev[0], s));
   }
   unsigned long long *counts = count ? w.tests : nullptr;
-  if (g->kind == GP_PIP) GP_TRY_HIP(launch_locate_pip(a, px, py, n, out_id, counts, s));
-  else GP_TRY_HIP(launch_locate_p2p(a, px, py, n, out_id, out_dist, counts, s));
+  GP_TRY_HIP(launch_locate(g->kind, a, LocRequest{px, py, out_id, out_dist, n, nullptr}, counts, s));
   if (stats) GP_TRY_HIP(hipEventRecord(ev[1], s));
   const bool segf = prec == GP_MIXED && g->d_cseg_off != nullptr;
   const int64_t *all = segf ? g->d_cell_edges : g->d_cell_edges_all;
   if (count)
-    GP_TRY_HIP(launch_locate_count(a, px, py, n, g->d_cand_off,
-                                   segf ? g->d_cell_segs : g->d_cell_edges, all, counts, s));
+    GP_TRY_HIP(launch_locate_count(a, px, py, n, g->d_cand_off, counted_tests(*g, prec), all,
+                                   counts, s));
   if (stats) {
     unsigned long long c[3] = {0, 0, 0};
     GP_TRY_HIP(hipStreamSynchronize(s));

@@ -176,6 +176,23 @@ struct LocArgs {
   double D2_next;           // the smallest double above fl(D*D)
 };
 
+// One query's points and results.
+struct LocRequest {
+  const double *px, *py;
+  int32_t *out_id;
+  double *out_dist;            // P2P
+  int64_t n;
+  unsigned long long *tests;   // served: pinned host memory for the candidate tests
+};
+
+// A served request on the device: what a captured launch reads, so that its graph can be
+// replayed for any buffers, and the partial sums of its candidate tests.
+constexpr int LOC_PARTS = 32;
+struct LocServed {
+  LocRequest r;
+  unsigned long long part[LOC_PARTS];
+};
+
 // What the build needs beside the grid: the (cell, feature) pairs' cells, the rings and the
 // vertices' y (PIP), and the largest coordinate magnitude of the vertices and the extent.
 struct LocBuild {
@@ -282,13 +299,17 @@ hipError_t launch_classify_pairs(const uint32_t *pair_cell, const int32_t *cand_
 hipError_t build_locator(Grid &g, const LocBuild &b, hipStream_t s);
 LocArgs locator_args(const Grid &g);
 bool uses_locator(const Grid &g, gp_precision prec);  // gp_api.cpp
+// The candidate tests of each cell that a query in this precision form counts (gp_api.cpp).
+const int64_t *counted_tests(const Grid &g, gp_precision prec);
 // counts (or null): three counters the query zeroes for launch_locate_count, which adds
 // the candidate tests of the points' cells, those over `all` (or null) and the points paired.
-hipError_t launch_locate_pip(const LocArgs &a, const double *px, const double *py, int64_t n,
-                             int32_t *out_id, unsigned long long *counts, hipStream_t s);
-hipError_t launch_locate_p2p(const LocArgs &a, const double *px, const double *py, int64_t n,
-                             int32_t *out_id, double *out_dist, unsigned long long *counts,
-                             hipStream_t s);
+hipError_t launch_locate(gp_kind kind, const LocArgs &a, const LocRequest &r,
+                         unsigned long long *counts, hipStream_t s);
+// A served request in two parts: its hand-over, and the query of at most `most` points and
+// its test count, which can be captured.
+hipError_t launch_serve_begin(LocServed *sv, const LocRequest &r, hipStream_t s);
+hipError_t launch_serve(gp_kind kind, const LocArgs &a, LocServed *sv, int64_t most,
+                        const int64_t *cell_tests, hipStream_t s);
 hipError_t launch_locate_count(const LocArgs &a, const double *px, const double *py, int64_t n,
                                const int32_t *cand_off, const int64_t *cell_tests,
                                const int64_t *all, unsigned long long *counts, hipStream_t s);

@@ -798,17 +798,50 @@ __device__ __forceinline__ void reset_counts(unsigned long long *counts) {
   if (counts && blockIdx.x == 0 && threadIdx.x < 3) counts[threadIdx.x] = 0;
 }
 
+// Adds a workgroup's candidate tests to one of the request's partial sums (a single counter
+// would queue the atomics of all workgroups).
+__device__ __forceinline__ void add_tests(LocServed *sv, unsigned long long t) {
+  __shared__ unsigned long long sum[256 / GP_WAVE];
+  for (int off = 32; off > 0; off >>= 1) t += __shfl_xor(t, off, GP_WAVE);
+  if (lane_id() == 0) sum[threadIdx.x / GP_WAVE] = t;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < 256 / GP_WAVE; ++w) t += sum[w];
+    if (t) atomicAdd(&sv->part[blockIdx.x % LOC_PARTS], t);
+  }
+}
+
+// Hands a request to the kernels that follow on the stream, and its test count to the host
+// after them (`tests` is pinned host memory).
+__global__ void k_serve_begin(LocServed *sv, LocRequest r) {
+  if (threadIdx.x == 0) sv->r = r;
+  for (uint32_t i = threadIdx.x; i < LOC_PARTS; i += blockDim.x) sv->part[i] = 0;
+}
+
+__global__ void k_serve_end(const LocServed *sv) {
+  unsigned long long t = threadIdx.x < LOC_PARTS ? sv->part[threadIdx.x] : 0;
+  for (int off = 32; off > 0; off >>= 1) t += __shfl_xor(t, off, GP_WAVE);
+  if (threadIdx.x == 0) *sv->r.tests = t;
+}
+
 // One point per lane; points and results pass the caches by (non-temporal), which hold the
 // index: 50M points 1.03 -> 0.98 ms.  Bound by the gathers of the index (a cell, then for a divided cell its
 // subcell, then for the few subcells with a list its slots); a point needs no sorting for
 // them, because a whole map's directory stays in the caches.  Region map of 1.5M vertices:
 // 50M points 6.7 -> 1.02 ms against the tiled refinement, 1M points on a plain grid
 // 2.3 -> 0.032 ms, 1,500 points 0.30 -> 0.008 ms.
-__global__ __launch_bounds__(256) void k_locate_pip(LocArgs a, const double *px,
-                                                    const double *py, int64_t n,
-                                                    int32_t *out_id,
-                                                    unsigned long long *counts) {
-  reset_counts(counts);
+// SERVED: the request comes from sv, for which the launch is at least large enough, and the
+// points' candidate tests are added to it.
+template <bool SERVED>
+__global__ __launch_bounds__(256) void k_locate_pip(LocArgs a, LocRequest r,
+                                                    unsigned long long *counts, LocServed *sv,
+                                                    const int64_t *cell_tests) {
+  if (SERVED) r = sv->r;
+  else reset_counts(counts);
+  const double *px = r.px, *py = r.py;
+  int32_t *out_id = r.out_id;
+  const int64_t n = r.n;
+  unsigned long long tests = 0;
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
        i += (int64_t)gridDim.x * blockDim.x) {
     const double x = __builtin_nontemporal_load(px + i), y = __builtin_nontemporal_load(py + i);
@@ -816,6 +849,7 @@ __global__ __launch_bounds__(256) void k_locate_pip(LocArgs a, const double *px,
     const int32_t c = locate_cell(a, x, y, ux, uy);
     int32_t ans = -1;
     if (c >= 0) {
+      if (SERVED) tests += (unsigned long long)cell_tests[c];
       const LocCell ce = a.cell[c];
       ans = (int32_t)ce.base;
       if (ce.m != LOC_CONST) {
@@ -841,6 +875,7 @@ __global__ __launch_bounds__(256) void k_locate_pip(LocArgs a, const double *px,
     }
     __builtin_nontemporal_store(ans, out_id + i);
   }
+  if (SERVED) add_tests(sv, tests);
 }
 
 // FP64 squared distance in the definition's operation order; a perpendicular quotient is
@@ -919,12 +954,18 @@ __device__ __forceinline__ void fetch64(const void *base, uint32_t idx, uint4 *l
 // Road map of 5.3M vertices: 200M points 167 -> 8.7 ms against the tiled refinement, 20M
 // with segment lists 5.91 -> 0.89 ms, 1,500 points 0.58 -> 0.009 ms; with each lane loading
 // its own records and an offset read ahead of them 13.2, 1.34 and 0.008 ms.
-__global__ __launch_bounds__(256) void k_locate_p2p(LocArgs a, const double *px,
-                                                    const double *py, int64_t n,
-                                                    int32_t *out_id, double *out_dist,
-                                                    unsigned long long *counts) {
+template <bool SERVED>
+__global__ __launch_bounds__(256) void k_locate_p2p(LocArgs a, LocRequest r,
+                                                    unsigned long long *counts, LocServed *sv,
+                                                    const int64_t *cell_tests) {
   __shared__ uint4 stage[256 / GP_WAVE][4 * GP_WAVE];
-  reset_counts(counts);
+  if (SERVED) r = sv->r;
+  else reset_counts(counts);
+  const double *px = r.px, *py = r.py;
+  int32_t *out_id = r.out_id;
+  double *out_dist = r.out_dist;
+  const int64_t n = r.n;
+  if (SERVED && blockIdx.x * (int64_t)blockDim.x >= n) return;
   uint4 *lds = stage[threadIdx.x / GP_WAVE];
   const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   const bool live = i < n;
@@ -1008,6 +1049,7 @@ __global__ __launch_bounds__(256) void k_locate_p2p(LocArgs a, const double *px,
       q = after(q, b.a[LOC_ENTRIES - 1], b.rest);
     }
   }
+  if (SERVED) add_tests(sv, c >= 0 ? (unsigned long long)cell_tests[c] : 0ull);
   if (live) {
     __builtin_nontemporal_store(id, out_id + i);
     __builtin_nontemporal_store(id >= 0 ? sqrt(best) : (double)INFINITY, out_dist + i);
@@ -1165,15 +1207,33 @@ static hipError_t launch_loc_sub_segs(const Grid &g, const uint32_t *first, cons
          g.y0, g.cs, g.nx, pad, g.D, slack, place, cnt, lim, block);
 }
 
-hipError_t launch_locate_pip(const LocArgs &a, const double *px, const double *py, int64_t n,
-                             int32_t *out_id, unsigned long long *counts, hipStream_t s) {
-  LAUNCH(k_locate_pip, blocks_for(n, 256, 1 << 24), 256, a, px, py, n, out_id, counts);
+hipError_t launch_locate(gp_kind kind, const LocArgs &a, const LocRequest &r,
+                         unsigned long long *counts, hipStream_t s) {
+  const unsigned b = (unsigned)((r.n + 255) / 256);
+  LocServed *none = nullptr;
+  const int64_t *no_tests = nullptr;
+  if (kind == GP_PIP) LAUNCH(k_locate_pip<false>, b, 256, a, r, counts, none, no_tests);
+  LAUNCH(k_locate_p2p<false>, b, 256, a, r, counts, none, no_tests);
 }
 
-hipError_t launch_locate_p2p(const LocArgs &a, const double *px, const double *py, int64_t n,
-                             int32_t *out_id, double *out_dist, unsigned long long *counts,
-                             hipStream_t s) {
-  LAUNCH(k_locate_p2p, (unsigned)((n + 255) / 256), 256, a, px, py, n, out_id, out_dist, counts);
+hipError_t launch_serve_begin(LocServed *sv, const LocRequest &r, hipStream_t s) {
+  LAUNCH(k_serve_begin, 1, GP_WAVE, sv, r);
+}
+
+hipError_t launch_serve(gp_kind kind, const LocArgs &a, LocServed *sv, int64_t most,
+                        const int64_t *cell_tests, hipStream_t s) {
+  const unsigned b = (unsigned)((most + 255) / 256);
+  LocRequest none{};
+  unsigned long long *no_counts = nullptr;
+  if (kind == GP_PIP)
+    hipLaunchKernelGGL(k_locate_pip<true>, dim3(b), dim3(256), 0, s, a, none, no_counts, sv,
+                       cell_tests);
+  else
+    hipLaunchKernelGGL(k_locate_p2p<true>, dim3(b), dim3(256), 0, s, a, none, no_counts, sv,
+                       cell_tests);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  LAUNCH(k_serve_end, 1, GP_WAVE, sv);
 }
 
 hipError_t launch_locate_count(const LocArgs &a, const double *px, const double *py, int64_t n,

@@ -162,3 +162,40 @@ def test_sizes_and_capture(gp, n):
                 wid, wd = oracle.p2p(w.geom, px, py, w.params.radius_D, og)
                 assert np.array_equal(out.cpu().numpy(), wid)
                 assert np.array_equal(dist.cpu().numpy(), wd)
+
+
+@pytest.mark.parametrize("graphs", [True, False])
+def test_served_while_the_tuning_changes(gp, graphs):
+    """One server, its blocks and their captured graphs reused while the grids go from the
+    locator to the tiled refinement and back: every request equals the oracle, and counts
+    the same tests on either path."""
+    wp = synth.config1(n_points=9_000, grid_n=3, seed_salt=5)
+    wl = synth.config2(n_points=9_000, n_lines=300, seed_salt=5)
+    grids = [gp.gp_build_grid(w.kind, w.geom, w.params) for w in (wp, wl)]
+    og = [oracle.build_grid(w.geom, w.params) for w in (wp, wl)]
+    srv = gp.Server(*grids, n_slots=2, slot_points=4096, mem_budget=1 << 30, use_graphs=graphs)
+    tests = []
+    for step, n in enumerate((9_000, 3_000, 1, 9_000, 2_000)):
+        for g in grids:
+            gp.gp_reset_tuning(g, "mixed")
+            if step in (1, 3):
+                gp.gp_set_tuning(g, "mixed", **gp.gp_get_tuning(g, "mixed"))
+        before = srv.stats()["tests"]
+        for w, o in zip((wp, wl), og):
+            px, py = w.px[-n:], w.py[-n:]
+            x, y = (torch.from_numpy(np.ascontiguousarray(v)).cuda() for v in (px, py))
+            out = torch.full((n + 8,), -9, dtype=torch.int32, device="cuda")
+            dist = torch.full((n + 8,), -9.0, dtype=torch.float64, device="cuda")
+            torch.cuda.synchronize()
+            if w.kind == "pip":
+                srv.wait(srv.submit("pip", x, y, out))
+                want = oracle.pip(w.geom, px, py, o), None
+            else:
+                srv.wait(srv.submit("p2p", x, y, out, dist))
+                want = oracle.p2p(w.geom, px, py, w.params.radius_D, o)
+                assert np.array_equal(dist[:n].cpu().numpy(), want[1]), (step, n)
+            assert np.array_equal(out[:n].cpu().numpy(), want[0]), (w.kind, step, n)
+            assert bool((out[n:] == -9).all()) and bool((dist[n:] == -9.0).all())
+        tests.append(srv.stats()["tests"] - before)
+    assert tests[0] == tests[3] > 0
+    srv.close()
