@@ -824,6 +824,29 @@ __global__ void k_serve_end(const LocServed *sv) {
   if (threadIdx.x == 0) *sv->r.tests = t;
 }
 
+// The answer of a list: per polygon its header and elements, by the definition's predicate.
+// A header's first element is read with it and every other one ahead of its turn, so that a
+// lane does not wait out each slot's latency (50M points 0.98 -> 0.92 ms, 1M 0.030 -> 0.028).
+__device__ __forceinline__ int32_t list_answer(const double4 *s, double x, double y) {
+  for (;;) {
+    const int4 hd = *(const int4 *)s;  // id, elements << 1 | parity, more, last
+    double4 e = s[1];                  // a header has an element
+    const int m = hd.y >> 1;
+    uint32_t odd = (uint32_t)hd.y & 1u;
+    for (int j = 1;; ++j) {
+      const double4 nx = s[j < m ? j + 1 : j];
+      const bool st = (e.y <= y) & (y < e.w);
+      const double lhs = (x - e.x) * (e.w - e.y), rhs = (e.z - e.x) * (y - e.y);
+      odd ^= (uint32_t)(st & (lhs < rhs));
+      if (j >= m) break;
+      e = nx;
+    }
+    if (odd) return hd.x;
+    if (!hd.z) return hd.w;
+    s += m + 1;
+  }
+}
+
 // One point per lane; points and results pass the caches by (non-temporal), which hold the
 // index: 50M points 1.03 -> 0.98 ms.  Bound by the gathers of the index (a cell, then for a divided cell its
 // subcell, then for the few subcells with a list its slots); a point needs no sorting for
@@ -855,21 +878,7 @@ __global__ __launch_bounds__(256) void k_locate_pip(LocArgs a, LocRequest r,
       if (ce.m != LOC_CONST) {
         ans = a.sub[subcell(ce.base, ce.m, ux, uy)];
         if (ans < -1) {
-          const double4 *s = a.slot + (uint32_t)(-(ans + 2));
-          for (;;) {
-            const int4 hd = *(const int4 *)s;  // id, elements << 1 | parity, more, last
-            const int m = hd.y >> 1;
-            uint32_t odd = (uint32_t)hd.y & 1u;
-            for (int j = 1; j <= m; ++j) {
-              const double4 e = s[j];
-              const bool st = (e.y <= y) & (y < e.w);
-              const double lhs = (x - e.x) * (e.w - e.y), rhs = (e.z - e.x) * (y - e.y);
-              odd ^= (uint32_t)(st & (lhs < rhs));
-            }
-            ans = odd ? hd.x : hd.w;
-            if (odd || !hd.z) break;
-            s += m + 1;
-          }
+          ans = list_answer(a.slot + (uint32_t)(-(ans + 2)), x, y);
         }
       }
     }
