@@ -171,10 +171,19 @@ def _ptr(t):
     return t.data_ptr()
 
 
+def _current_stream():
+    """The current device's current stream, as an integer.  The handle alone, where torch
+    gives it: building a Stream object takes 2.8 us, a third of a small query's call."""
+    import torch
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    if raw is None or not torch.cuda.is_initialized():
+        return torch.cuda.current_stream().cuda_stream
+    return raw(torch._C._cuda_getDevice())
+
+
 def _stream(stream):
     if stream is None:
-        import torch
-        return torch.cuda.current_stream().cuda_stream
+        return _current_stream()
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream

@@ -164,6 +164,15 @@ def test_sizes_and_capture(gp, n):
                 assert np.array_equal(dist.cpu().numpy(), wd)
 
 
+def test_default_stream_is_the_current_one(gp):
+    """A call without a stream runs on torch's current one, also inside a stream context."""
+    s = torch.cuda.Stream()
+    assert gp._current_stream() == torch.cuda.current_stream().cuda_stream
+    with torch.cuda.stream(s):
+        assert gp._current_stream() == s.cuda_stream
+    assert gp._current_stream() == torch.cuda.current_stream().cuda_stream
+
+
 @pytest.mark.parametrize("graphs", [True, False])
 def test_served_while_the_tuning_changes(gp, graphs):
     """One server, its blocks and their captured graphs reused while the grids go from the
