@@ -539,19 +539,20 @@ def main():
         "grid_build_ms": build_ms,
         "tuning": {"pip": gp.gp_get_tuning(grid3, prec), "p2p": gp.gp_get_tuning(grid4, prec)},
     }
-    # the same two queries on the library's default path
+    # the same two queries on the library's default path, into outputs of their own
     tuned = [(g, gp.gp_get_tuning(g, prec)) for g in (grid3, grid4)]
-    ids = id3.clone(), id4.clone(), d4.clone()
     for g, _ in tuned:
         gp.gp_reset_tuning(g, prec)
-    step(False)
-    loc = [step(True) for _ in range(5)]
+    oid3, oid4, od4 = torch.empty_like(id3), torch.empty_like(id4), torch.empty_like(d4)
+    loc = [(gp.gp_pip(grid3, x3, y3, oid3, prec, ws3, stream, True)["ms_total"],
+            gp.gp_p2p(grid4, x4, y4, oid4, od4, prec, ws4, stream, True)["ms_total"])
+           for _ in range(6)][1:]
     detail["locator"] = {
-        "pip_ms": float(np.median([a["ms_total"] for a, _ in loc])),
-        "p2p_ms": float(np.median([b["ms_total"] for _, b in loc])),
-        "same_results": bool(torch.equal(ids[0], id3) and torch.equal(ids[1], id4)
-                             and torch.equal(ids[2], d4))}
-    del ids
+        "pip_ms": float(np.median([a for a, _ in loc])),
+        "p2p_ms": float(np.median([b for _, b in loc])),
+        "same_results": bool(torch.equal(oid3, id3) and torch.equal(oid4, id4)
+                             and torch.equal(od4, d4))}
+    del oid3, oid4, od4
     for g, t in tuned:
         gp.gp_set_tuning(g, prec, **t)
     # Measured ceilings of this GPU (micro-kernels in the library): FP32 FMA with VGPR
