@@ -104,9 +104,12 @@ struct alignas(16) LocSegCell {
   uint32_t base, m;
   double reach;
 };
+struct LocEntry {
+  uint32_t a, b;
+  int32_t seg;
+};
 struct alignas(64) LocBlock {
-  uint32_t a[LOC_ENTRIES], b[LOC_ENTRIES];
-  int32_t seg[LOC_ENTRIES];
+  LocEntry e[LOC_ENTRIES];
   float rest;
 };
 static_assert(sizeof(LocBlock) == 64, "one aligned 64-byte line");

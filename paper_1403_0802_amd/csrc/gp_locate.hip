@@ -632,8 +632,8 @@ template <bool EMIT>
 __global__ __launch_bounds__(256) void k_loc_sub_segs(
     const uint32_t *first, const int32_t *list, const double4 *edge64, const int2 *group,
     uint32_t ngroups, const LocSegCell *cell, double x0, double y0, double cs, int32_t nx,
-    double pad, double D, double slack, const int32_t *place, uint32_t *cnt, double2 *lim,
-    LocBlock *block) {
+    double pad, double D, double slack, const int32_t *place, double *glim, uint32_t *cnt,
+    double2 *lim, LocBlock *block) {
   __shared__ double4 sa[256 / GP_WAVE][GP_WAVE];  // a.x, a.y, d.x, d.y
   __shared__ double si[256 / GP_WAVE][GP_WAVE];   // 1 / |d|^2
   __shared__ uint2 sl[256 / GP_WAVE][GP_WAVE];    // the entry
@@ -655,15 +655,20 @@ __global__ __launch_bounds__(256) void k_loc_sub_segs(
   const double px = ox + ((double)g.sx + 0.5) * a, py = oy + ((double)g.sy + 0.5) * a;
   const uint32_t at = ce.base + ((uint32_t)g.sy << ce.m) + (uint32_t)g.sx;
   const uint32_t l0 = first[c], l1 = first[c + 1];
-  // the group's limit
-  double gmin = INFINITY;
-  for (uint32_t l = l0 + lane; l < l1; l += GP_WAVE) {
-    const double4 e = edge64[list[l]];
-    const double dx = e.z - e.x, dy = e.w - e.y, L2 = dx * dx + dy * dy;
-    gmin = fmin(gmin, seg_dist2(gx, gy, e.x, e.y, dx, dy, L2 > 0.0 ? 1.0 / L2 : 0.0));
+  double glim2;  // the group's limit
+  if constexpr (!EMIT) {
+    double gmin = INFINITY;
+    for (uint32_t l = l0 + lane; l < l1; l += GP_WAVE) {
+      const double4 e = edge64[list[l]];
+      const double dx = e.z - e.x, dy = e.w - e.y, L2 = dx * dx + dy * dy;
+      gmin = fmin(gmin, seg_dist2(gx, gy, e.x, e.y, dx, dy, L2 > 0.0 ? 1.0 / L2 : 0.0));
+    }
+    for (int off = 32; off > 0; off >>= 1) gmin = fmin(gmin, __shfl_xor(gmin, off, GP_WAVE));
+    glim2 = keep_limit2(gmin, rg, D, slack);
+    if (lane == 0) glim[w] = glim2;
+  } else {
+    glim2 = glim[w];
   }
-  for (int off = 32; off > 0; off >>= 1) gmin = fmin(gmin, __shfl_xor(gmin, off, GP_WAVE));
-  const double glim2 = keep_limit2(gmin, rg, D, slack);
   // the group's segments, broadcast one by one
   auto sweep = [&](auto &&meet) {
     for (uint32_t l = l0; l < l1; l += GP_WAVE) {
@@ -712,17 +717,14 @@ __global__ __launch_bounds__(256) void k_loc_sub_segs(
   } else {
     const double2 dl = g.act ? lim[at] : make_double2(0.0, 0.0);
     const double lim2 = dl.y, step = (sqrt(lim2) - dl.x) * (1.0 / LOC_RINGS);
-    double t2[LOC_RINGS];  // squared inner radius of each ring
-#pragma unroll
-    for (int i = 0; i < LOC_RINGS; ++i) {
-      const double t = dl.x + (double)i * step;
-      t2[i] = t * t;
-    }
+    // FP32, in units of the limit: within 2^-21 of the true place, which from ring 1 on is
+    // under 2^-18 of the distance (against 7 FP64 compares an entry: 6.3 -> 5.6 ms for a map of
+    // 5.3M segments in 200 x 200 cells)
+    const double unit = lim2 > 1e-290 ? 1.0 / lim2 : 0.0;
+    const float inner = (float)(dl.x * sqrt(unit)), rings = (float)LOC_RINGS / (1.0f - inner);
     auto ring_of = [&](double d2) {
-      int i = 0;
-#pragma unroll
-      for (int k = 1; k < LOC_RINGS; ++k) i += d2 > t2[k] ? 1 : 0;
-      return i;
+      const float t = (__builtin_amdgcn_sqrtf((float)(d2 * unit)) - inner) * rings;
+      return (int)fminf(fmaxf(t, 0.0f), (float)(LOC_RINGS - 1));
     };
     const uint32_t tid = threadIdx.x;
 #pragma unroll
@@ -742,7 +744,7 @@ __global__ __launch_bounds__(256) void k_loc_sub_segs(
     if (g.act) {
       // a block's `rest` is at most the distance to the centre of any later entry, in steps
       // of the frame; the last block's ends the list
-      const double f = LOC_UNITS / (cs + 2.0 * ce.reach) * (1.0 - 0x1p-16);
+      const double f = LOC_UNITS / (cs + 2.0 * ce.reach) * (1.0 - 0x1p-15);
       auto rest = [&](uint32_t e) {  // of the block before the one entry e begins
         int i = 0;
         while (i + 1 < LOC_RINGS && ring[i + 1][tid] <= e) ++i;
@@ -751,24 +753,16 @@ __global__ __launch_bounds__(256) void k_loc_sub_segs(
       block[2 * at].rest = rest(LOC_ENTRIES);
       LocBlock &l = block[2 * at + 1];
       l.rest = rest(LOC_LINE);
-      l.a[LOC_ENTRIES - 1] = more;
-      l.b[LOC_ENTRIES - 1] = 0u;
-      l.seg[LOC_ENTRIES - 1] = -1;
+      l.e[LOC_ENTRIES - 1] = LocEntry{more, 0u, -1};
       uint32_t e = LOC_LINE;
       for (; e < n; e += LOC_ENTRIES) block[block_of(e)].rest = rest(e + LOC_ENTRIES);
-      for (uint32_t k = n; k < e; ++k) {  // places without an entry
-        LocBlock &o = block[block_of(k)];
-        o.a[slot_of(k)] = o.b[slot_of(k)] = 0u;
-        o.seg[slot_of(k)] = -1;
-      }
+      for (uint32_t k = n; k < e; ++k)  // places without an entry
+        block[block_of(k)].e[slot_of(k)] = LocEntry{0u, 0u, -1};
     }
     sweep([&](int q, double d2) {
       if (g.act && !(d2 > lim2)) {
         const uint32_t e = ring[ring_of(d2)][tid]++;
-        LocBlock &o = block[block_of(e)];
-        o.a[slot_of(e)] = sl[wave][q].x;
-        o.b[slot_of(e)] = sl[wave][q].y;
-        o.seg[slot_of(e)] = sg[wave][q];
+        block[block_of(e)].e[slot_of(e)] = LocEntry{sl[wave][q].x, sl[wave][q].y, sg[wave][q]};
       }
     });
   }
@@ -848,11 +842,14 @@ __device__ __forceinline__ int32_t list_answer(const double4 *s, double x, doubl
 }
 
 // One point per lane; points and results pass the caches by (non-temporal), which hold the
-// index: 50M points 1.03 -> 0.98 ms.  Bound by the gathers of the index (a cell, then for a divided cell its
-// subcell, then for the few subcells with a list its slots); a point needs no sorting for
-// them, because a whole map's directory stays in the caches.  Region map of 1.5M vertices:
-// 50M points 6.7 -> 1.02 ms against the tiled refinement, 1M points on a plain grid
-// 2.3 -> 0.032 ms, 1,500 points 0.30 -> 0.008 ms.
+// index: 50M points 1.03 -> 0.98 ms.  Bound by the gathers of the index (a cell, then for a
+// divided cell its subcell, then for the few subcells with a list its slots): 50M points miss
+// the L2 for 133 bytes each, 7.2 TB/s, with 70 to 90 lines in flight per compute unit.  The
+// points and results alone take 0.23 ms of the 0.92, the cells 0.16, the subcells 0.36 and
+// the lists 0.17.  Sorting the points by cell would save less than the sort costs, because a
+// whole map's directory nearly fits the caches.  Region map of 1.5M vertices, against the
+// tiled refinement: 50M points 6.5 -> 0.92 ms, 1M points on a plain grid 1.6 -> 0.028 ms,
+// 1,500 points 0.42 -> 0.005 ms.
 // SERVED: the request comes from sv, for which the launch is at least large enough, and the
 // points' candidate tests are added to it.
 template <bool SERVED>
@@ -960,8 +957,12 @@ __device__ __forceinline__ void fetch64(const void *base, uint32_t idx, uint4 *l
 // the third's distance); the entries within twice the error of the nearest, one as a rule,
 // are decided by their exact distances (smaller distance, then smaller polyline).  Bound by
 // the gathers of lists and segments.
-// Road map of 5.3M vertices: 200M points 167 -> 8.7 ms against the tiled refinement, 20M
-// with segment lists 5.91 -> 0.89 ms, 1,500 points 0.58 -> 0.009 ms; with each lane loading
+// Of 8.5 ms for 200M points, points, results and cells take 2.1, the first block of the lists
+// 1.9, their further blocks 1.1 and the exact segments 3.4; the L2 misses for 310 bytes a
+// point, 7.2 TB/s.  Sorting the points first (by cell 4.5 ms, by 20 x 20 cells 5.0) costs
+// more than it saves (3.3 to 6.2 ms, and results scattered back).
+// Road map of 5.3M vertices, against the tiled refinement: 200M points 164 -> 8.5 ms, 20M
+// with segment lists 5.87 -> 0.87 ms, 1,500 points 0.52 -> 0.008 ms; with each lane loading
 // its own records and an offset read ahead of them 13.2, 1.34 and 0.008 ms.
 template <bool SERVED>
 __global__ __launch_bounds__(256) void k_locate_p2p(LocArgs a, LocRequest r,
@@ -1016,12 +1017,12 @@ __global__ __launch_bounds__(256) void k_locate_p2p(LocArgs a, LocRequest r,
   for (uint32_t q = q0; ballot(q != LOC_NONE);) {
     fetch64(a.block, q, lds, w);
     if (q != LOC_NONE) {
-      meet(w[0].x, w[1].y, w[2].z);
-      meet(w[0].y, w[1].z, w[2].w);
-      meet(w[0].z, w[1].w, w[3].x);
-      meet(w[0].w, w[2].x, w[3].y);
-      meet(w[1].x, w[2].y, w[3].z);
-      q = after(q, w[1].x, __uint_as_float(w[3].w));
+      meet(w[0].x, w[0].y, w[0].z);
+      meet(w[0].w, w[1].x, w[1].y);
+      meet(w[1].z, w[1].w, w[2].x);
+      meet(w[2].y, w[2].z, w[2].w);
+      meet(w[3].x, w[3].y, w[3].z);
+      q = after(q, w[3].x, __uint_as_float(w[3].w));
     }
   }
   double best = a.D2_next;  // accept d2 <= fl(D*D); later only strictly smaller
@@ -1053,9 +1054,9 @@ __global__ __launch_bounds__(256) void k_locate_p2p(LocArgs a, LocRequest r,
     for (uint32_t q = q0; q != LOC_NONE;) {
       const LocBlock &b = a.block[q];
       for (int t = 0; t < LOC_ENTRIES; ++t)
-        if (b.seg[t] >= 0 && entry_d2(qx, qy, b.a[t], b.b[t]) <= lim2)
-          take(a.lseg[b.seg[t]].e, a.lseg[b.seg[t]].f);
-      q = after(q, b.a[LOC_ENTRIES - 1], b.rest);
+        if (b.e[t].seg >= 0 && entry_d2(qx, qy, b.e[t].a, b.e[t].b) <= lim2)
+          take(a.lseg[b.e[t].seg].e, a.lseg[b.e[t].seg].f);
+      q = after(q, b.e[LOC_ENTRIES - 1].a, b.rest);
     }
   }
   if (SERVED) add_tests(sv, c >= 0 ? (unsigned long long)cell_tests[c] : 0ull);
@@ -1206,14 +1207,14 @@ static hipError_t launch_loc_segments(const Grid &g, const uint32_t *order, cons
 static hipError_t launch_loc_sub_segs(const Grid &g, const uint32_t *first, const int32_t *list,
                                       const int2 *group, uint32_t ngroups,
                                       const LocSegCell *cell, double pad, double slack,
-                                      const int32_t *place, uint32_t *cnt, double2 *lim, LocBlock *block,
-                                      hipStream_t s) {
+                                      const int32_t *place, double *glim, uint32_t *cnt,
+                                      double2 *lim, LocBlock *block, hipStream_t s) {
   const unsigned b = (ngroups + 3) / 4;
   if (block)
     LAUNCH(k_loc_sub_segs<true>, b, 256, first, list, g.d_edge64, group, ngroups, cell, g.x0,
-           g.y0, g.cs, g.nx, pad, g.D, slack, place, cnt, lim, block);
+           g.y0, g.cs, g.nx, pad, g.D, slack, place, glim, cnt, lim, block);
   LAUNCH(k_loc_sub_segs<false>, b, 256, first, list, g.d_edge64, group, ngroups, cell, g.x0,
-         g.y0, g.cs, g.nx, pad, g.D, slack, place, cnt, lim, block);
+         g.y0, g.cs, g.nx, pad, g.D, slack, place, glim, cnt, lim, block);
 }
 
 hipError_t launch_locate(gp_kind kind, const LocArgs &a, const LocRequest &r,
@@ -1431,23 +1432,25 @@ hipError_t build_p2p(Grid &g, double pad, double slack, hipStream_t s) {
   const size_t ns = (size_t)cost[0];
   const uint32_t ng = (uint32_t)cost[3];
   Places p2;
-  const size_t o_group = p2.add((size_t)ng * 8), o_lim = p2.add(ns * 16),
+  const size_t o_group = p2.add((size_t)ng * 8), o_glim = p2.add((size_t)ng * 8),
+               o_lim = p2.add(ns * 16),
                o_soff = p2.add((ns + 1) * 4), o_stmp = p2.add(scan_tmp_elems(ns + 1) * 4);
   LOC_NEED(b2.alloc(p2.bytes));
   int2 *group = b2.as<int2>(o_group);
+  double *glim = b2.as<double>(o_glim);
   double2 *lim = b2.as<double2>(o_lim);
   uint32_t *soff = b2.as<uint32_t>(o_soff);
   LOC_TRY(launch_exclusive_scan_u32(nsub, nsub, nc + 1, tmp, s));
   LOC_TRY(launch_loc_groups(g, nsub, cell, (uint32_t *)sum, group, s));
   total = 0;
   if (ns) {
-    LOC_TRY(launch_loc_sub_segs(g, cnt, list, group, ng, cell, pad, slack, place, soff, lim,
+    LOC_TRY(launch_loc_sub_segs(g, cnt, list, group, ng, cell, pad, slack, place, glim, soff, lim,
                                 nullptr, s));
     LOC_TRY(scan_counts(soff, ns, kMaxBlocks, sum, b2.as<uint32_t>(o_stmp), &total, s));
     LOC_NEED(total <= kMaxBlocks && LOC_ENTRIES * total <= kMaxMeanEntries * (int64_t)ns);
     LOC_NEED(blocks.alloc((size_t)(2 * ns + total) * sizeof(LocBlock)));
     LOC_TRY(launch_loc_add(soff, ns, 2 * (uint32_t)ns, s));
-    LOC_TRY(launch_loc_sub_segs(g, cnt, list, group, ng, cell, pad, slack, place, soff, lim,
+    LOC_TRY(launch_loc_sub_segs(g, cnt, list, group, ng, cell, pad, slack, place, glim, soff, lim,
                                 blocks.as<LocBlock>(), s));
   }
   LOC_TRY(hipStreamSynchronize(s));
