@@ -172,7 +172,9 @@ __device__ __forceinline__ uint32_t group_count(uint32_t m) {
 }
 
 // log2 of the subdivision for a cell with E elements: about E / 4 subcells along a side, so
-// that a boundary crossing the cell leaves a few elements in the subcells it meets.
+// that a boundary crossing the cell leaves a few elements in the subcells it meets.  At
+// half the limits 50M points of the region map take 0.89 instead of 0.92 ms with 28% more
+// memory and a 7% longer build, at 2.5 times the limits 1.02 ms with 23% less memory.
 __device__ __forceinline__ uint32_t pip_shape(uint32_t E, uint32_t cap) {
   const uint32_t m = E <= 4 ? 2u : E <= 24 ? 3u : E <= 96 ? 4u : E <= 384 ? 5u : 6u;
   return m < cap ? m : cap;
