@@ -887,8 +887,10 @@ __global__ __launch_bounds__(256) void k_locate_pip(LocArgs a, LocRequest r,
 }
 
 // FP64 squared distance in the definition's operation order; a perpendicular quotient is
-// divided out only where it can still come below `best` (cc >= fl(best * L2) (1 + 2^-49)
-// implies cc / L2 > best).
+// divided out only where it can still come below `best`: cc > fl(fl(best * L2) (1 + 2^-49))
+// implies cc / L2 > best, also where the product underflows (a subnormal product is within
+// half a unit of best * L2, and cc is at least a whole unit above it).  Equality divides: with
+// D = 0 the product is 0 for every short segment, and cc is 0 for a point on one.
 __device__ __forceinline__ double exact_d2(double x, double y, const double4 r, double best) {
   const double dx = r.z - r.x, dy = r.w - r.y;
   const double wx = x - r.x, wy = y - r.y;
@@ -901,7 +903,7 @@ __device__ __forceinline__ double exact_d2(double x, double y, const double4 r, 
   }
   const double cr = wx * dy - wy * dx;
   const double cc = cr * cr;
-  return cc < (best * L2) * (1.0 + 0x1p-49) ? cc / L2 : INFINITY;
+  return cc > (best * L2) * (1.0 + 0x1p-49) ? INFINITY : cc / L2;
 }
 
 // Squared distance to an entry, in steps of its frame: FP32 on whole numbers below 2^16.

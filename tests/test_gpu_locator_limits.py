@@ -1,0 +1,68 @@
+"""Where the locator's rules end.  Answers are compared with the oracle's bit for bit."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_1403_0802_amd import synth
+from tests import pins
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def gp():
+    if not torch.cuda.is_available():
+        pytest.skip("needs a GPU")
+    from paper_1403_0802_amd import gp as gpmod
+    return gpmod
+
+
+def dev(*arrays):
+    return [torch.from_numpy(np.ascontiguousarray(a)).cuda() for a in arrays]
+
+
+def p2p_equal(gp, grid, geom, params, px, py, tunings=(None,), precs=("fp64", "mixed")):
+    want_id, want_d = oracle.p2p(geom, px, py, params.radius_D, oracle.build_grid(geom, params))
+    x, y = dev(px, py)
+    for prec in precs:
+        for tuning in tunings:
+            gp.gp_reset_tuning(grid, prec)
+            if tuning is not None:
+                gp.gp_set_tuning(grid, prec, **tuning)
+            got_id, got_d = (v.cpu().numpy() for v in gp.run(grid, x, y, prec))
+            bad = np.flatnonzero((got_id != want_id) | (got_d != want_d))
+            assert bad.size == 0, (params, prec, tuning, bad.size, px[bad[:3]], py[bad[:3]],
+                                   got_id[bad[:3]], want_id[bad[:3]], got_d[bad[:3]])
+        gp.gp_reset_tuning(grid, prec)
+    return want_id, want_d
+
+
+ZERO_TUNINGS = {"locator": (None,)}
+
+
+@pytest.mark.parametrize("D", [0.0, 1e-170, 1e-161, 1e-155])
+@pytest.mark.parametrize("cells", [1, 8])
+@pytest.mark.parametrize("path", list(ZERO_TUNINGS))
+def test_range_zero_on_the_inside_of_short_segments(gp, path, cells, D):
+    """At a range whose square is 0 or subnormal, points exactly on segments shorter than
+    0.7 (dyadic coordinates, so that a point on one has a cross product of 0) are in range at
+    distance 0, although the product of D^2 and the segment's square underflows to 0."""
+    rng = np.random.default_rng(11)
+    lines, pts = [], []
+    for k in range(200):
+        ax, ay = rng.integers(0, 64, 2) / 64.0
+        step = [(1, 0), (0, 1), (1, 1), (1, -1)][k % 4]
+        m = 8.0 * 2.0 ** -int(rng.integers(6, 10))  # 8 steps of 1/64 to 1/512
+        lines.append([(ax, ay), (ax + m * step[0], ay + m * step[1])])
+        t = m * rng.integers(0, 9, 40) / 8.0
+        pts.append(np.stack([ax + t * step[0], ay + t * step[1]], 1))
+    g = pins.polylines(lines)
+    p = np.concatenate(pts)
+    near = p + rng.choice([-1.0, 0.0, 1.0], p.shape) * 2.0 ** -40
+    px, py = np.concatenate([p, near, rng.uniform(0, 1, (500, 2))]).T.copy()
+    params = synth.GridParams(cell_size=1.0 / cells, radius_D=D, x0=0.0, y0=0.0, nx=cells, ny=cells)
+    for options in ({}, {"prestage": 1}, {"segment_filter": 1}):
+        grid = gp.gp_build_grid("p2p", g, synth.GridParams(**{**params.__dict__, **options}))
+        want_id, want_d = p2p_equal(gp, grid, g, params, px, py, ZERO_TUNINGS[path])
+    assert np.sum(want_d == 0.0) > 3_000 and np.any(want_id < 0)
