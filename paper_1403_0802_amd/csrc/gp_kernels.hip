@@ -1919,7 +1919,8 @@ __device__ void p2p_vp_item(const RefineArgs &a, const Item it, int32_t *win) {
           } else {
             const double cr = wx * dy - wy * dx;
             const double cc = cr * cr;
-            d2 = cc < (best[j] * L2) * (1.0 + 0x1p-49) ? cc / L2 : INFINITY;
+            // strictly above the product, which may underflow to 0 (D = 0)
+            d2 = cc > (best[j] * L2) * (1.0 + 0x1p-49) ? INFINITY : cc / L2;
           }
           if (d2 < best[j]) {
             best[j] = d2;
@@ -2037,10 +2038,11 @@ __device__ void p2p64_item(const RefineArgs &a, const Item it, SegRec64 *lds, in
           double d2 = ca ? da[j] : db;
           const bool cp = !ca & !cb;
           // The perpendicular case divides only when its quotient could still beat the
-          // current best: cc >= fl(best * L2p) >= fl(best*L2)*(1+2^-49) implies
-          // cc/L2 > best.
+          // current best: cc > fl(best * L2p), L2p >= L2 * (1 + 2^-49), implies cc/L2 > best.
+          // Equality divides: with D = 0 the product underflows to 0, and cc is 0 for a
+          // point on the segment.
           d2 = cp ? INFINITY : d2;
-          if (cp && cc < best[j] * r.L2p) d2 = cc / r.L2;
+          if (cp && !(cc > best[j] * r.L2p)) d2 = cc / r.L2;
           if (d2 < best[j]) { best[j] = d2; bid[j] = f; }
           wx[j] = ex;
           wy[j] = ey;
@@ -2859,7 +2861,8 @@ __global__ __launch_bounds__(256) void k_recheck_p2p(RefineArgs a) {
     for (int32_t k = a.cand_off[cell]; k < a.cand_off[cell + 1]; ++k) {
       const int32_t f = a.cand_id[k];
       // a segment matters only if its d2 can beat thr = min(best, next(D2)); its
-      // perpendicular quotient is divided out only when cc < fl(thr*L2)*(1+2^-49)
+      // perpendicular quotient is divided out unless cc > fl(thr*L2)*(1+2^-49), a product
+      // that underflows to 0 with D = 0
       const double thr = fmin(best, a.D2_next);
       double pd = INFINITY;
       for (int32_t e = a.eoff[f] + (int32_t)lane; e < a.eoff[f + 1]; e += GP_WAVE) {
@@ -2877,7 +2880,7 @@ __global__ __launch_bounds__(256) void k_recheck_p2p(RefineArgs a) {
         } else {
           const double c = wx * dy - wy * dx;
           const double cc = c * c;
-          d2 = cc < (thr * L2) * (1.0 + 0x1p-49) ? cc / L2 : INFINITY;
+          d2 = cc > (thr * L2) * (1.0 + 0x1p-49) ? INFINITY : cc / L2;
         }
         pd = fmin(pd, d2);
       }

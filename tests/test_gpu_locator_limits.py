@@ -38,7 +38,9 @@ def p2p_equal(gp, grid, geom, params, px, py, tunings=(None,), precs=("fp64", "m
     return want_id, want_d
 
 
-ZERO_TUNINGS = {"locator": (None,)}
+ZERO_TUNINGS = {"locator": (None,),
+                "tiled": (dict(vp_points=-1), dict(vp_points=-1, points_per_lane=1),
+                          dict(vp_points=64), dict(waves_per_item=2, vp_points=-1))}
 
 
 @pytest.mark.parametrize("D", [0.0, 1e-170, 1e-161, 1e-155])
