@@ -551,10 +551,14 @@ __global__ __launch_bounds__(256) void k_loc_p2p_cells(const uint32_t *first, co
 
 // Segments by value with their polyline, 64 bytes each, in the order of the index's cells (by
 // the cell of the midpoint), so that segments near each other share lines and pages.
+// *flag becomes 1 where a segment that is not a point has |d|^2 below min_L2.
 __global__ void k_loc_seg_keys(const double4 *edge64, int32_t n, double x0, double y0, double cs,
-                               int32_t nx, int32_t ny, uint32_t *key) {
+                               int32_t nx, int32_t ny, double min_L2, uint32_t *key,
+                               uint32_t *flag) {
   for (int32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
     const double4 e = edge64[i];
+    const double dx = e.z - e.x, dy = e.w - e.y;
+    if ((dx != 0.0 || dy != 0.0) && dx * dx + dy * dy < min_L2) atomicOr(flag, 1u);
     const double fx = floor((0.5 * (e.x + e.z) - x0) / cs), fy = floor((0.5 * (e.y + e.w) - y0) / cs);
     const int32_t x = (int32_t)fmin(fmax(fx, 0.0), (double)(nx - 1));
     const int32_t y = (int32_t)fmin(fmax(fy, 0.0), (double)(ny - 1));
@@ -1193,9 +1197,10 @@ static hipError_t launch_loc_add(uint32_t *v, size_t n, uint32_t d, hipStream_t 
   LAUNCH(k_loc_add, blocks_for((int64_t)n, 256, 8192), 256, v, n, d);
 }
 
-static hipError_t launch_loc_seg_keys(const Grid &g, uint32_t *key, hipStream_t s) {
+static hipError_t launch_loc_seg_keys(const Grid &g, double min_L2, uint32_t *key, uint32_t *flag,
+                                      hipStream_t s) {
   LAUNCH(k_loc_seg_keys, blocks_for(g.nedges, 256, 8192), 256, g.d_edge64, g.nedges, g.x0, g.y0,
-         g.cs, g.nx, g.ny, key);
+         g.cs, g.nx, g.ny, min_L2, key, flag);
 }
 
 static hipError_t launch_loc_polylines(const Grid &g, int32_t *f, hipStream_t s) {
@@ -1275,6 +1280,13 @@ constexpr int64_t kMaxCells = int64_t(1) << 26;
 constexpr int64_t kMaxBuildTests = int64_t(1) << 33;
 constexpr int64_t kMaxMeanEntries = 64;
 constexpr uint32_t kLocTarget = 8;  // P2P: entries per subcell aimed at
+// P2P: the definition's (w x d)^2 / |d|^2 holds a distance only while its square is neither
+// lost to underflow (an error of 2^-537 / |d|, below 2^-80 cells when |d|^2 is at least
+// kMinLen2 and at least kMinLen2 / cs^2) nor overflows (64 M^4 < 2^1024, M the largest
+// coordinate).  Beyond that its FP64 value may order the segments otherwise than their
+// distances do, which is what an index goes by.
+constexpr double kMinLen2 = 0x1p-900;
+constexpr double kMaxP2PCoord = 0x1p250;
 
 struct Buf {
   void *p = nullptr;
@@ -1407,7 +1419,13 @@ hipError_t build_p2p(Grid &g, double pad, double slack, hipStream_t s) {
     uint32_t *keys = nullptr, *order = nullptr;
     int bits = 1;
     while (bits < 31 && (1 << bits) < g.ncells) ++bits;
-    LOC_TRY(launch_loc_seg_keys(g, b1.as<uint32_t>(o_kA), s));
+    // a segment too short for its cross products (kMinLen2): the grid goes without
+    uint32_t tiny = 0;
+    LOC_TRY(launch_fill_u32((uint32_t *)sum, 0u, 1, s));
+    LOC_TRY(launch_loc_seg_keys(g, kMinLen2 * std::max(1.0, 1.0 / (g.cs * g.cs)),
+                                b1.as<uint32_t>(o_kA), (uint32_t *)sum, s));
+    LOC_TRY(read_back(&tiny, sum, 4, s));
+    LOC_NEED(!tiny);
     LOC_TRY(launch_loc_polylines(g, b1.as<int32_t>(o_poly), s));
     LOC_TRY(launch_radix_sort(b1.as<uint32_t>(o_kA), b1.as<uint32_t>(o_kB),
                               b1.as<uint32_t>(o_vA), b1.as<uint32_t>(o_vB), nseg, bits, true,
@@ -1472,7 +1490,7 @@ hipError_t build_p2p(Grid &g, double pad, double slack, hipStream_t s) {
 hipError_t build_locator(Grid &g, const LocBuild &b, hipStream_t s) {
   if (g.ncells > kMaxCells || !(b.max_coord < 1e150) || !(g.cs > 1e-140)) return hipSuccess;
   // P2P: the frames' steps are whole only where a coordinate's rounding is far below one
-  if (g.kind == GP_P2P && !(b.max_coord < g.cs * 0x1p28)) return hipSuccess;
+  if (g.kind == GP_P2P && !(b.max_coord < std::min(g.cs * 0x1p28, kMaxP2PCoord))) return hipSuccess;
   // pads: as the MBBs', and over 1000 times the rounding of a point's cell and subcell
   const double pad = g.cs * 0x1p-20 + b.max_coord * 0x1p-40;
   if (g.kind == GP_PIP) return build_pip(g, b, pad, s);

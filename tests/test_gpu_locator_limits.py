@@ -68,3 +68,32 @@ def test_range_zero_on_the_inside_of_short_segments(gp, path, cells, D):
         grid = gp.gp_build_grid("p2p", g, synth.GridParams(**{**params.__dict__, **options}))
         want_id, want_d = p2p_equal(gp, grid, g, params, px, py, ZERO_TUNINGS[path])
     assert np.sum(want_d == 0.0) > 3_000 and np.any(want_id < 0)
+
+
+@pytest.mark.parametrize("scale", [1e-136, 1e-100, 1e-74, 1e-60, 1e60, 1e74, 1e80, 1e100, 1e140])
+def test_p2p_magnitudes(gp, scale):
+    """Coordinates at which (w x d)^2 = (distance * length)^2 underflows or overflows: the
+    definition's answer is then that of its FP64 operations, not of the geometry, so only a
+    path that evaluates every candidate gives it."""
+    rng = np.random.default_rng(31)
+    lines = [rng.uniform(0, 8, 2) + np.cumsum(rng.normal(0, 0.3, (int(rng.integers(2, 20)), 2)), 0)
+             for _ in range(80)]
+    lines += [np.array([(0.0, 1.0 + k), (8.0, 1.5 + k)]) for k in range(6)]
+    g = pins.polylines([[(x * scale, y * scale) for x, y in p] for p in lines])
+    params = synth.GridParams(cell_size=0.5 * scale, radius_D=2.0 * scale, x0=0.0, y0=0.0,
+                              nx=16, ny=16)
+    px, py = scale * rng.uniform(-0.2, 8.2, (2, 4_000))
+    grid = gp.gp_build_grid("p2p", g, params)
+    p2p_equal(gp, grid, g, params, px, py)
+
+
+def test_p2p_segments_below_the_square_root_of_the_smallest_double(gp):
+    """In an ordinary grid, a segment so short that its square is subnormal: a point level
+    with its inside gets the quotient of two subnormal numbers."""
+    g = pins.polylines([[(0.0, 0.0), (2e-161, 0.0)], [(-0.5, 1.0), (0.5, 1.0)],
+                        [(0.0, -0.75), (3e-161, -0.75)]])
+    params = synth.GridParams(cell_size=1.0, radius_D=4.0, x0=-2.0, y0=-2.0, nx=4, ny=4)
+    x = np.repeat(np.linspace(0.0, 4e-161, 81), 41)
+    y = np.tile(np.linspace(-1.5, 1.5, 41), 81)
+    grid = gp.gp_build_grid("p2p", g, params)
+    p2p_equal(gp, grid, g, params, x, y)
