@@ -60,6 +60,44 @@ __device__ __forceinline__ int32_t tiled_rank(int32_t c, int32_t nx, int32_t ny)
   return ty * nx + tx * h + (y - ty) * w + (x - tx);
 }
 
+// What the first passes of the build visit: the edges of every cell's candidate polygons, or
+// the segments of its candidates' near ranges (`near`, P2P).  out[0] += their number over all
+// cells, out[1] = max(that of a cell).  One wave per cell; an atomic per workgroup.
+__global__ __launch_bounds__(256) void k_loc_work(const int32_t *cand_off, const int32_t *cand_id,
+                                                  const int32_t *eoff, const int2 *near,
+                                                  int32_t ncells, unsigned long long *out) {
+  __shared__ unsigned long long part[2][256 / GP_WAVE];
+  const int32_t nw = (int32_t)(gridDim.x * (blockDim.x / GP_WAVE));
+  unsigned long long all = 0, most = 0;
+  for (int32_t c = uniform((int32_t)(blockIdx.x * (blockDim.x / GP_WAVE) + threadIdx.x / GP_WAVE));
+       c < ncells; c += nw) {
+    const int32_t k1 = cand_off[c + 1];
+    unsigned long long t = 0;
+    for (int32_t k = cand_off[c] + (int32_t)lane_id(); k < k1; k += GP_WAVE) {
+      const int32_t f = cand_id[k];
+      t += (unsigned long long)(near ? near[k].y - near[k].x : eoff[f + 1] - eoff[f]);
+    }
+    for (int off = 32; off > 0; off >>= 1) t += __shfl_xor(t, off, GP_WAVE);
+    all += t;
+    most = most > t ? most : t;
+  }
+  if (lane_id() == 0) {
+    part[0][threadIdx.x / GP_WAVE] = all;
+    part[1][threadIdx.x / GP_WAVE] = most;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < 256 / GP_WAVE; ++w) {
+      all += part[0][w];
+      most = most > part[1][w] ? most : part[1][w];
+    }
+    if (all) {
+      atomicAdd(out, all);
+      atomicMax(out + 1, most);
+    }
+  }
+}
+
 // ------------------------------------------------------------------------- PIP build
 
 // x of the stand-ins for chains of edges right of a subcell: far right of any point (the
@@ -162,7 +200,7 @@ __global__ __launch_bounds__(256) void k_loc_pip_pairs(
 // Elements of every cell up to the first polygon that contains the whole cell, and the
 // cell's answer when there are none.  eoffs[k] are the pairs' first elements.  shape
 // [c] = log2 k, or LOC_CONST; cost[0] += subcells, cost[1] += subcells * elements,
-// cost[2] += groups of the list builder.
+// cost[2] += groups of the list builder, cost[3] = max(elements).
 constexpr uint32_t LOC_CONST = 0xffu;
 
 // A wave of the list builders takes a group of subcells: an 8 x 8 block, or the whole of a
@@ -187,7 +225,7 @@ __global__ __launch_bounds__(256) void k_loc_pip_cells(const int32_t *cand_off,
                                                        LocCell *cell,
                                                        unsigned long long *cost) {
   const int32_t ncells = nx * ny;
-  unsigned long long s0 = 0, s1 = 0, s2 = 0;
+  unsigned long long s0 = 0, s1 = 0, s2 = 0, most = 0;
   for (int32_t c = blockIdx.x * blockDim.x + threadIdx.x; c <= ncells;
        c += gridDim.x * blockDim.x) {
     uint32_t E = 0;
@@ -209,6 +247,7 @@ __global__ __launch_bounds__(256) void k_loc_pip_cells(const int32_t *cand_off,
       s0 += q;
       s1 += (unsigned long long)q * E;
       s2 += E ? group_count(m) : 0u;
+      most = most > E ? most : E;
     } else {
       nsub[c] = 0;
     }
@@ -217,11 +256,14 @@ __global__ __launch_bounds__(256) void k_loc_pip_cells(const int32_t *cand_off,
     s0 += __shfl_xor(s0, off, GP_WAVE);
     s1 += __shfl_xor(s1, off, GP_WAVE);
     s2 += __shfl_xor(s2, off, GP_WAVE);
+    const unsigned long long o = __shfl_xor(most, off, GP_WAVE);
+    most = most > o ? most : o;
   }
   if (lane_id() == 0 && s1) {
     atomicAdd(cost, s0);
     atomicAdd(cost + 1, s1);
     atomicAdd(cost + 2, s2);
+    atomicMax(cost + 3, most);
   }
 }
 
@@ -509,7 +551,7 @@ __device__ __forceinline__ uint32_t p2p_shape(uint32_t n, uint32_t target, uint3
 
 // reach of a cell: no point of it has its nearest segment within D farther away.
 // cost[0] += subcells, cost[1] += subcells * segments, cost[2] += expected entries,
-// cost[3] += groups of the list builder.
+// cost[3] += groups of the list builder, cost[4] = max(segments).
 __global__ __launch_bounds__(256) void k_loc_p2p_cells(const uint32_t *first, const double *cmin,
                                                        int32_t nx, int32_t ny, double r,
                                                        double D, double slack, uint32_t target,
@@ -517,7 +559,7 @@ __global__ __launch_bounds__(256) void k_loc_p2p_cells(const uint32_t *first, co
                                                        LocSegCell *cell,
                                                        unsigned long long *cost) {
   const int32_t ncells = nx * ny;
-  unsigned long long s0 = 0, s1 = 0, s2 = 0, s3 = 0;
+  unsigned long long s0 = 0, s1 = 0, s2 = 0, s3 = 0, most = 0;
   for (int32_t c = blockIdx.x * blockDim.x + threadIdx.x; c <= ncells;
        c += gridDim.x * blockDim.x) {
     if (c < ncells) {
@@ -531,6 +573,7 @@ __global__ __launch_bounds__(256) void k_loc_p2p_cells(const uint32_t *first, co
       s1 += (unsigned long long)q * n;
       s2 += (unsigned long long)n << m;
       s3 += n ? group_count(m) : 0u;
+      most = most > n ? most : n;
     } else {
       nsub[c] = 0;
     }
@@ -540,12 +583,15 @@ __global__ __launch_bounds__(256) void k_loc_p2p_cells(const uint32_t *first, co
     s1 += __shfl_xor(s1, off, GP_WAVE);
     s2 += __shfl_xor(s2, off, GP_WAVE);
     s3 += __shfl_xor(s3, off, GP_WAVE);
+    const unsigned long long o = __shfl_xor(most, off, GP_WAVE);
+    most = most > o ? most : o;
   }
   if (lane_id() == 0 && s0) {
     atomicAdd(cost, s0);
     atomicAdd(cost + 1, s1);
     atomicAdd(cost + 2, s2);
     atomicAdd(cost + 3, s3);
+    atomicMax(cost + 4, most);
   }
 }
 
@@ -1129,6 +1175,11 @@ __global__ __launch_bounds__(256) void k_locate_count(LocArgs a, const double *p
     return hipGetLastError();                                 \
   } while (0)
 
+static hipError_t launch_loc_work(const Grid &g, unsigned long long *out, hipStream_t s) {
+  LAUNCH(k_loc_work, blocks_for(g.ncells, 4, 2048), 256, g.d_cand_off, g.d_cand_id, g.d_eoff,
+         g.kind == GP_P2P ? g.d_near : nullptr, g.ncells, out);
+}
+
 static hipError_t launch_loc_ring_prev(const int32_t *rvo, int32_t nr, int32_t *prev, hipStream_t s) {
   if (nr <= 0) return hipSuccess;
   LAUNCH(k_loc_ring_prev, blocks_for(nr, 1, 65536), 64, rvo, nr, prev);
@@ -1278,6 +1329,14 @@ constexpr int64_t kMaxElems = int64_t(1) << 26;     // 2 GiB while building
 constexpr int64_t kMaxSubcells = int64_t(1) << 27;  // 512 MiB
 constexpr int64_t kMaxCells = int64_t(1) << 26;
 constexpr int64_t kMaxBuildTests = int64_t(1) << 33;
+// The first passes sweep the candidates' edges of every cell, each one's by one wave (P2P) or by
+// one for a polygon, and a wave sweeps a cell's elements or segments again for each group.  At
+// the limits that is, beside a build without a locator: 2^36 edges in all 0.3 s (7.6e10 edge
+// visits, twice, 0.39 s, about two tiled queries of one point per cell), 2^22 of a cell 0.1 s,
+// 2^20 elements of a cell 0.1 s.
+constexpr int64_t kMaxPairEdges = int64_t(1) << 36;
+constexpr int64_t kMaxCellEdges = int64_t(1) << 22;
+constexpr int64_t kMaxCellElems = int64_t(1) << 20;
 constexpr int64_t kMaxMeanEntries = 64;
 constexpr uint32_t kLocTarget = 8;  // P2P: entries per subcell aimed at
 // P2P: the definition's (w x d)^2 / |d|^2 holds a distance only while its square is neither
@@ -1339,6 +1398,17 @@ hipError_t scan_counts(uint32_t *cnt, size_t n, int64_t most, unsigned long long
   return launch_exclusive_scan_u32(cnt, cnt, n + 1, tmp, s);
 }
 
+// Whether the first passes stay within their limits.
+hipError_t work_fits(const Grid &g, unsigned long long *sum, bool *fits, hipStream_t s) {
+  unsigned long long work[2] = {0, 0};
+  LOC_TRY(launch_fill_u32((uint32_t *)sum, 0u, 4, s));
+  LOC_TRY(launch_loc_work(g, sum, s));
+  LOC_TRY(read_back(work, sum, 16, s));
+  *fits = work[0] <= (unsigned long long)kMaxPairEdges &&
+          work[1] <= (unsigned long long)kMaxCellEdges;
+  return hipSuccess;
+}
+
 hipError_t build_pip(Grid &g, const LocBuild &b, double pad, hipStream_t s) {
   const size_t np = (size_t)g.npairs, nc = (size_t)g.ncells;
   Buf b1, b2, elems, cells, subs, slots;
@@ -1353,6 +1423,9 @@ hipError_t build_pip(Grid &g, const LocBuild &b, double pad, hipStream_t s) {
   uint8_t *par = b1.as<uint8_t>(o_par);
   unsigned long long *sum = b1.as<unsigned long long>(o_sum);
   LocCell *cell = cells.as<LocCell>();
+  bool fits = false;
+  LOC_TRY(work_fits(g, sum, &fits, s));
+  LOC_NEED(fits);
   int64_t total = 0;
   LOC_TRY(launch_loc_ring_prev(b.ring_off, b.n_rings, prev, s));
   if (np) LOC_TRY(launch_loc_pip_pairs(g, b.pair_cell, b.vy, prev, pad, cnt, par, nullptr, s));
@@ -1361,11 +1434,12 @@ hipError_t build_pip(Grid &g, const LocBuild &b, double pad, hipStream_t s) {
   double4 *elem = elems.as<double4>();
   if (total) LOC_TRY(launch_loc_pip_pairs(g, b.pair_cell, b.vy, prev, pad, cnt, par, elem, s));
   // the finest subdivision whose size and build stay within the limits
-  unsigned long long cost[3] = {0, 0, 0};
+  unsigned long long cost[4] = {0, 0, 0, 0};
   for (int cap = 6; cap >= 0; --cap) {
-    LOC_TRY(launch_fill_u32((uint32_t *)sum, 0u, 6, s));
+    LOC_TRY(launch_fill_u32((uint32_t *)sum, 0u, 8, s));
     LOC_TRY(launch_loc_pip_cells(g, cnt, par, (uint32_t)cap, nsub, cell, sum, s));
-    LOC_TRY(read_back(cost, sum, 24, s));
+    LOC_TRY(read_back(cost, sum, 32, s));
+    LOC_NEED(cost[3] <= (unsigned long long)kMaxCellElems);
     if (cost[0] <= (unsigned long long)kMaxSubcells && cost[1] <= (unsigned long long)kMaxBuildTests)
       break;
     LOC_NEED(cap > 0);
@@ -1415,6 +1489,9 @@ hipError_t build_p2p(Grid &g, double pad, double slack, hipStream_t s) {
   unsigned long long *sum = b1.as<unsigned long long>(o_sum);
   int32_t *place = b1.as<int32_t>(o_place);
   LocSegCell *cell = cells.as<LocSegCell>();
+  bool fits = false;
+  LOC_TRY(work_fits(g, sum, &fits, s));
+  LOC_NEED(fits);
   if (nseg) {  // the segments in the order of the cells
     uint32_t *keys = nullptr, *order = nullptr;
     int bits = 1;
@@ -1440,11 +1517,12 @@ hipError_t build_p2p(Grid &g, double pad, double slack, hipStream_t s) {
   LOC_NEED(total <= kMaxEntries && lists.alloc((size_t)total * 4));
   int32_t *list = lists.as<int32_t>();
   if (total) LOC_TRY(launch_loc_cell_segs(g, r, slack, cnt, cmin, list, s));
-  unsigned long long cost[4] = {0, 0, 0, 0};
+  unsigned long long cost[5] = {0, 0, 0, 0, 0};
   for (uint32_t target = kLocTarget;; target *= 2) {
-    LOC_TRY(launch_fill_u32((uint32_t *)sum, 0u, 8, s));
+    LOC_TRY(launch_fill_u32((uint32_t *)sum, 0u, 10, s));
     LOC_TRY(launch_loc_p2p_cells(g, cnt, cmin, r, slack + pad, target, 5u, nsub, cell, sum, s));
-    LOC_TRY(read_back(cost, sum, 32, s));
+    LOC_TRY(read_back(cost, sum, 40, s));
+    LOC_NEED(cost[4] <= (unsigned long long)kMaxCellElems);
     if (cost[0] <= (unsigned long long)kMaxLines &&
         cost[1] <= (unsigned long long)kMaxBuildTests &&
         cost[2] <= (unsigned long long)kMaxEntries)

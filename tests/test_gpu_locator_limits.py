@@ -1,4 +1,6 @@
 """Where the locator's rules end.  Answers are compared with the oracle's bit for bit."""
+import time
+
 import numpy as np
 import pytest
 
@@ -97,3 +99,55 @@ def test_p2p_segments_below_the_square_root_of_the_smallest_double(gp):
     y = np.tile(np.linspace(-1.5, 1.5, 41), 81)
     grid = gp.gp_build_grid("p2p", g, params)
     p2p_equal(gp, grid, g, params, x, y)
+
+
+def on_locator(stats):
+    """The locator sorts no points; the tiled refinement's pairing takes time."""
+    return stats["ms_pairing"] == 0.0
+
+
+def detour(n):
+    """The box (0.1, 0.1)-(0.9, 0.9) with ``n`` edges, all but four of which zigzag far below
+    the unit square, from which its left side comes back."""
+    k = n - 4
+    x = np.linspace(0.1, 0.9, k + 1)
+    y = np.where(np.arange(k + 1) % 2 == 0, -9.0, -10.0)
+    return np.concatenate([[0.9, 0.9, 0.1], x])[:n], np.concatenate([[0.1, 0.9, 0.9], y])[:n]
+
+
+@pytest.mark.parametrize("vertices,cells,has", [(1 << 22, 4, True), ((1 << 22) + 1, 4, False),
+                                                (200_000, 512, True), (400_000, 512, False)])
+def test_pip_grids_with_too_many_candidate_edges(gp, vertices, cells, has):
+    """One polygon over the whole grid: the edges of the (cell, polygon) pairs, which the
+    locator's build visits, exceed its limit for one cell (2^22) or for the grid (2^36)."""
+    x, y = detour(vertices)
+    geom = synth.Geometry("pip", np.array([0, vertices]), x, y, np.array([0, 1]))
+    params = synth.GridParams(cell_size=1.0 / cells, x0=0.0, y0=0.0, nx=cells, ny=cells)
+    t0 = time.perf_counter()
+    grid = gp.gp_build_grid("pip", geom, params)
+    print("vertices", vertices, "cells", cells, "build s", time.perf_counter() - t0, flush=True)
+    px, py = np.random.default_rng(5).uniform(0, 1, (2, 2_000))
+    got, st = gp.run(grid, *dev(px, py), "fp64", stats=True)
+    assert on_locator(st) == has
+    assert np.array_equal(got.cpu().numpy(), oracle.pip(geom, px, py, oracle.build_grid(geom, params)))
+
+
+@pytest.mark.parametrize("segments,has", [(1 << 22, True), ((1 << 22) + 1, False)])
+def test_p2p_grids_with_too_many_segments_in_a_cell(gp, segments, has):
+    """A polyline that leaves the grid's only cell and comes back: its near range there is all
+    of it, as many segments as the build sweeps for a cell or one more."""
+    x = np.linspace(-20.0, 20.0, segments + 1)
+    y = np.where(np.arange(segments + 1) % 2 == 0, 30.0, 31.0)
+    x[:2], y[:2] = (0.25, 0.75), (0.25, 0.25)
+    x[-2:], y[-2:] = (0.75, 0.25), (0.75, 0.75)
+    geom = synth.Geometry("p2p", np.array([0, segments + 1]), x, y, None)
+    params = synth.GridParams(cell_size=1.0, radius_D=0.125, x0=0.0, y0=0.0, nx=1, ny=1)
+    t0 = time.perf_counter()
+    grid = gp.gp_build_grid("p2p", geom, params)
+    print("segments", segments, "build s", time.perf_counter() - t0, flush=True)
+    px, py = np.random.default_rng(6).uniform(0, 1, (2, 500))
+    got_id, got_d, st = gp.run(grid, *dev(px, py), "fp64", stats=True)
+    assert on_locator(st) == has
+    want_id, want_d = oracle.p2p(geom, px, py, 0.125, oracle.build_grid(geom, params))
+    assert np.array_equal(got_id.cpu().numpy(), want_id)
+    assert np.array_equal(got_d.cpu().numpy(), want_d)
