@@ -338,6 +338,16 @@ extern "C" gp_status gp_build_grid(gp_kind kind, const gp_geometry *geom,
   g->ncells = (int32_t)(nx * ny);
   const int32_t ncells = g->ncells;
 
+  // The locator is built after everything that the caller asked the grid to hold (PIP: while
+  // the pairs' cells are there): it does without where the memory left does not take it.
+  LocBuild lb;
+  lb.pair_cell = nullptr;
+  lb.ring_off = d_rvo.as<int32_t>();
+  lb.n_rings = (int32_t)nr;
+  lb.vy = d_y.as<double>();
+  lb.max_coord = std::max({max_coord, std::fabs(x0), std::fabs(y0),
+                           std::fabs(x0 + (double)nx * cs), std::fabs(y0 + (double)ny * cs)});
+
   // rasterise the MBBs: per-feature counts, offsets, emit, stable sort by cell
   {
     DevBuf d_cnt, d_tmp;
@@ -460,14 +470,8 @@ extern "C" gp_status gp_build_grid(gp_kind kind, const gp_geometry *geom,
                                        g->d_prec_off, g->d_pcnt, g->d_precs, s));
       GP_TRY_HIP_G(hipStreamSynchronize(s));
     }
-    LocBuild lb;
     lb.pair_cell = skeys;
-    lb.ring_off = d_rvo.as<int32_t>();
-    lb.n_rings = (int32_t)nr;
-    lb.vy = d_y.as<double>();
-    lb.max_coord = std::max({max_coord, std::fabs(x0), std::fabs(y0),
-                             std::fabs(x0 + (double)nx * cs), std::fabs(y0 + (double)ny * cs)});
-    GP_TRY_HIP_G(build_locator(*g, lb, s));
+    if (kind == GP_PIP) GP_TRY_HIP_G(build_locator(*g, lb, s));
   }
   if (kind == GP_P2P && params->p2p_segment_filter && nedges > 0) {
     // (cell, segment) pairs: every segment's box, expanded by D and padded like the MBBs,
@@ -536,6 +540,7 @@ extern "C" gp_status gp_build_grid(gp_kind kind, const gp_geometry *geom,
                                  g->d_recU, g->d_recV, g->d_cellE, s));
     GP_TRY_HIP_G(hipStreamSynchronize(s));
   }
+  if (kind == GP_P2P) GP_TRY_HIP_G(build_locator(*g, lb, s));
 #undef GP_TRY_HIP_G
   *out = g;
   return GP_OK;

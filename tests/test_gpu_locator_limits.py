@@ -151,3 +151,36 @@ def test_p2p_grids_with_too_many_segments_in_a_cell(gp, segments, has):
     want_id, want_d = oracle.p2p(geom, px, py, 0.125, oracle.build_grid(geom, params))
     assert np.array_equal(got_id.cpu().numpy(), want_id)
     assert np.array_equal(got_d.cpu().numpy(), want_d)
+
+
+def test_a_grid_that_fits_without_a_locator_is_built(gp):
+    """With room on the device for a grid's segment records but not for the locator beside
+    them, the grid is built, and answers without one."""
+    g = synth.config4_geometry(n_lines=60_000, seed_salt=2)
+    params = synth.GridParams(cell_size=100.0, radius_D=100.0, nx=400, ny=400, prestage=1)
+    px, py = synth.config4_points(50_000, seed_salt=4)
+    want = oracle.p2p(g, px, py, 100.0, oracle.build_grid(g, params))
+    x, y = dev(px, py)
+    torch.cuda.empty_cache()
+    grid = gp.gp_build_grid("p2p", g, params)
+    assert on_locator(gp.run(grid, x, y, "mixed", stats=True)[-1])
+    all_bytes = grid.info()["device_bytes"]
+    del grid
+    plain = gp.gp_build_grid("p2p", g, synth.GridParams(**{**params.__dict__, "prestage": 0}))
+    records = all_bytes - plain.info()["device_bytes"]  # without the locator's and the rest
+    rest = plain.info()["device_bytes"]
+    del plain
+    torch.cuda.empty_cache()
+    print("grid", all_bytes, "records", records, flush=True)
+    assert records > 1 << 30 and rest > 1 << 29
+    free = torch.cuda.mem_get_info()[0]
+    # what stays free holds the records and half of the rest (the locator is most of it)
+    hog = torch.empty(free - records - rest // 2, dtype=torch.uint8, device="cuda")
+    grid = gp.gp_build_grid("p2p", g, params)
+    held = grid.info()["device_bytes"]
+    del hog
+    torch.cuda.empty_cache()
+    got_id, got_d, st = gp.run(grid, x, y, "mixed", stats=True)
+    assert held < all_bytes and not on_locator(st)
+    assert np.array_equal(got_id.cpu().numpy(), want[0])
+    assert np.array_equal(got_d.cpu().numpy(), want[1])
