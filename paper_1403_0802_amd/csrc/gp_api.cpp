@@ -710,6 +710,22 @@ bool uses_locator(const Grid &g, gp_precision prec) {
   return (g.d_loc_cell || g.d_loc_scell) && !g.tune_explicit[prec];
 }
 
+// Whether the results' memory meets the points'.  The locator writes a point's results while
+// other points are still to be read; the tiled refinement has read all of them by then, so it
+// takes such a query.  Distances exactly over x or y are a lane's own point: they count as
+// apart unless `own` is false (the counters of a query read the points again).
+bool results_over_points(int64_t n, const double *px, const double *py, const int32_t *out_id,
+                         const double *out_dist, bool own) {
+  const uintptr_t pts[2] = {(uintptr_t)px, (uintptr_t)py};
+  const uintptr_t id = (uintptr_t)out_id, di = (uintptr_t)out_dist;
+  const uintptr_t eight = (uintptr_t)n * 8, four = (uintptr_t)n * 4;
+  for (const uintptr_t p : pts) {
+    if (id < p + eight && p < id + four) return true;
+    if (di && di < p + eight && p < di + eight && !(own && di == p)) return true;
+  }
+  return false;
+}
+
 const int64_t *counted_tests(const Grid &g, gp_precision prec) {
   return prec == GP_MIXED && g.d_cseg_off ? g.d_cell_segs : g.d_cell_edges;
 }
@@ -772,7 +788,9 @@ static gp_status run_query(const gp_grid *g, gp_kind kind, int64_t n, const doub
   const size_t need = workspace_layout(*g, n, prec, ws, &w);
   if (!ws || ws_bytes < need)
     return set_error(GP_E_INVALID_ARG, "workspace too small: %zu bytes needed", need);
-  if (!override_tuning && uses_locator(*g, prec))
+  if (!override_tuning && uses_locator(*g, prec) &&
+      !results_over_points(n, px, py, out_id, kind == GP_P2P ? out_dist : nullptr,
+                           !stats && !count))
     return run_locator(g, n, px, py, out_id, out_dist, prec, w, s, stats, count);
   gp_tuning t = override_tuning ? *override_tuning : g->tune[prec];
   // The library default's persistent queue has a cost at the end of every launch (each

@@ -302,6 +302,10 @@ hipError_t launch_classify_pairs(const uint32_t *pair_cell, const int32_t *cand_
 hipError_t build_locator(Grid &g, const LocBuild &b, hipStream_t s);
 LocArgs locator_args(const Grid &g);
 bool uses_locator(const Grid &g, gp_precision prec);  // gp_api.cpp
+// Whether a query's results overlap its points in memory, other than distances that lie
+// exactly over a coordinate where `own` says that these do not count (gp_api.cpp).
+bool results_over_points(int64_t n, const double *px, const double *py, const int32_t *out_id,
+                         const double *out_dist, bool own);
 // The candidate tests of each cell that a query in this precision form counts (gp_api.cpp).
 const int64_t *counted_tests(const Grid &g, gp_precision prec);
 // counts (or null): three counters the query zeroes for launch_locate_count, which adds

@@ -274,7 +274,10 @@ static gp_status enqueue_chunk(gp_server *srv, Lane &ln, Request *r, Block *blk,
   const gp_grid *g = srv->grid[r->kind];
   const int64_t b = blk->bucket;
   const gp_precision prec = (gp_precision)o.precision;
-  if (o.inputs_on_device && uses_locator(*(const Grid *)g, prec)) {
+  // (of the whole request: a chunk's results may lie over another chunk's points)
+  if (o.inputs_on_device && uses_locator(*(const Grid *)g, prec) &&
+      !results_over_points(r->n, r->px, r->py, r->out_id,
+                           r->kind == GP_P2P ? r->out_dist : nullptr, true)) {
     // The locator needs no workspace and no order of the points: it runs on the request's own
     // buffers.  A chunk is handed over through the block's memory, so the captured query
     // replays for any buffers and sizes of its bucket.

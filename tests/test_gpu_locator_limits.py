@@ -184,3 +184,48 @@ def test_a_grid_that_fits_without_a_locator_is_built(gp):
     assert held < all_bytes and not on_locator(st)
     assert np.array_equal(got_id.cpu().numpy(), want[0])
     assert np.array_equal(got_d.cpu().numpy(), want[1])
+
+
+@pytest.mark.parametrize("kind", ["pip", "p2p"])
+def test_results_over_the_points(gp, kind):
+    """Results written into the points' own memory (ids over x, distances over y): a query
+    has read every point before, and its counters are those of the points."""
+    n = 400_003
+    w = (synth.config1(n_points=n, grid_n=6) if kind == "pip"
+         else synth.config2(n_points=n, n_lines=4_000))
+    grid = gp.gp_build_grid(kind, w.geom, w.params)
+    og = oracle.build_grid(w.geom, w.params)
+    ws = gp.new_workspace(grid, n, "mixed")
+    x, y = dev(w.px, w.py)
+    want_st = gp.run(grid, x, y, "mixed", ws=ws, stats=True)[-1]
+    srv = gp.Server(*((grid, None) if kind == "pip" else (None, grid)), n_slots=1,
+                    slot_points=1 << 19, mem_budget=2 << 30)
+    for how in ("query", "stats", "noalloc", "served", "distances only"):
+        x, y = dev(w.px, w.py)
+        ids = x.view(torch.int32)[:n] if how != "distances only" else torch.empty_like(
+            x, dtype=torch.int32)
+        if how == "served":
+            torch.cuda.synchronize()
+            before = srv.stats()["tests"]
+            srv.wait(srv.submit(kind, x, y, ids, y if kind == "p2p" else None))
+            assert srv.stats()["tests"] - before == want_st["tests"]
+        elif how == "noalloc":
+            gp.check(gp.lib.gp_query_noalloc(
+                grid.handle, grid.kind, n, x.data_ptr(), y.data_ptr(), ids.data_ptr(),
+                y.data_ptr() if kind == "p2p" else None, gp.PRECISIONS["mixed"],
+                torch.cuda.current_stream().cuda_stream))
+        elif kind == "pip":
+            st = gp.gp_pip(grid, x, y, ids, "mixed", ws, stats=how == "stats")
+        else:
+            st = gp.gp_p2p(grid, x, y, ids, y, "mixed", ws, stats=how == "stats")
+        torch.cuda.synchronize()
+        if kind == "pip":
+            assert np.array_equal(ids.cpu().numpy(), oracle.pip(w.geom, w.px, w.py, og)), how
+        else:
+            want_id, want_d = oracle.p2p(w.geom, w.px, w.py, w.params.radius_D, og)
+            assert np.array_equal(ids.cpu().numpy(), want_id), how
+            assert np.array_equal(y.cpu().numpy(), want_d), how
+        if how == "stats":
+            for key in ("n_points", "n_paired", "tests"):
+                assert st[key] == want_st[key], key
+    srv.close()
