@@ -732,9 +732,9 @@ const int64_t *counted_tests(const Grid &g, gp_precision prec) {
 
 // The query on the locator; both precision forms, whose results are the same bits.
 // `count` leaves the test counters in the workspace (stats implies it).
-static gp_status run_locator(const gp_grid *g, int64_t n, const double *px, const double *py,
-                             int32_t *out_id, double *out_dist, gp_precision prec,
-                             const Workspace &w, hipStream_t s, gp_stats *stats, bool count) {
+gp_status run_locator(const gp_grid *g, int64_t n, const double *px, const double *py,
+                      int32_t *out_id, double *out_dist, gp_precision prec, const Workspace &w,
+                      hipStream_t s, gp_stats *stats, bool count) {
   const LocArgs a = locator_args(*g);
   hipEvent_t ev[2] = {};
   if (stats) {
@@ -770,8 +770,7 @@ static gp_status run_locator(const gp_grid *g, int64_t n, const double *px, cons
 static gp_status run_query(const gp_grid *g, gp_kind kind, int64_t n, const double *px,
                            const double *py, int32_t *out_id, double *out_dist,
                            gp_precision prec, void *ws, size_t ws_bytes, hipStream_t s,
-                           gp_stats *stats, const gp_tuning *override_tuning,
-                           bool count = false) {
+                           gp_stats *stats, const gp_tuning *override_tuning) {
   if (!g) return set_error(GP_E_INVALID_ARG, "null grid");
   if (g->kind != kind)
     return set_error(GP_E_INVALID_ARG, "grid was built for the other operation");
@@ -790,8 +789,8 @@ static gp_status run_query(const gp_grid *g, gp_kind kind, int64_t n, const doub
     return set_error(GP_E_INVALID_ARG, "workspace too small: %zu bytes needed", need);
   if (!override_tuning && uses_locator(*g, prec) &&
       !results_over_points(n, px, py, out_id, kind == GP_P2P ? out_dist : nullptr,
-                           !stats && !count))
-    return run_locator(g, n, px, py, out_id, out_dist, prec, w, s, stats, count);
+                           !stats))
+    return run_locator(g, n, px, py, out_id, out_dist, prec, w, s, stats, false);
   gp_tuning t = override_tuning ? *override_tuning : g->tune[prec];
   // The library default's persistent queue has a cost at the end of every launch (each
   // workgroup finds the queues empty) that only a large query amortises: below
@@ -915,8 +914,8 @@ static gp_status run_query(const gp_grid *g, gp_kind kind, int64_t n, const doub
 gp_status run_query_tuned(const gp_grid *g, gp_kind kind, int64_t n, const double *px,
                           const double *py, int32_t *out_id, double *out_dist,
                           gp_precision prec, void *ws, size_t ws_bytes, hipStream_t s,
-                          gp_stats *stats, const gp_tuning *t, bool count) {
-  return run_query(g, kind, n, px, py, out_id, out_dist, prec, ws, ws_bytes, s, stats, t, count);
+                          gp_stats *stats, const gp_tuning *t) {
+  return run_query(g, kind, n, px, py, out_id, out_dist, prec, ws, ws_bytes, s, stats, t);
 }
 
 }  // namespace gp

@@ -16,7 +16,7 @@ gp_status set_error(gp_status code, const char *fmt, ...);
 gp_status run_query_tuned(const gp_grid *g, gp_kind kind, int64_t n, const double *px,
                           const double *py, int32_t *out_id, double *out_dist,
                           gp_precision prec, void *ws, size_t ws_bytes, hipStream_t s,
-                          gp_stats *stats, const gp_tuning *t, bool count);
+                          gp_stats *stats, const gp_tuning *t);
 }  // namespace gp
 
 using namespace gp;
@@ -70,5 +70,5 @@ extern "C" gp_status gp_query_noalloc(const gp_grid *grid, gp_kind kind, int64_t
   if (rc) return rc;
   return run_query_tuned(grid, kind, n, px, py, out_id, out_dist, prec, ws,
                          (size_t)GP_NOALLOC_SCRATCH_BYTES, (hipStream_t)hip_stream, nullptr,
-                         nullptr, false);
+                         nullptr);
 }

@@ -26,7 +26,9 @@
 // and replays it for every later chunk of its shape.  Buckets are powers of two from
 // 1024 up to slot_points; a chunk of m points runs the graph of bucket b >= m with the
 // tail [m, b) of its inputs filled with NaN, which the filter leaves unpaired (no
-// refinement work).  Graphs capture the grid's kernel configuration at first use.
+// refinement work).  Graphs capture the grid's kernel configuration at first use; a block
+// drops its graph when a chunk takes another of the three paths (tiled refinement, locator on
+// the block's copies, locator in place).
 //
 // One server thread admits chunks, enqueues their copies and graph launches, and polls
 // the streams' events to complete chunks and tickets.  A ticket is released (its
@@ -56,7 +58,10 @@ gp_status set_error(gp_status code, const char *fmt, ...);
 gp_status run_query_tuned(const gp_grid *g, gp_kind kind, int64_t n, const double *px,
                           const double *py, int32_t *out_id, double *out_dist,
                           gp_precision prec, void *ws, size_t ws_bytes, hipStream_t s,
-                          gp_stats *stats, const gp_tuning *t, bool count);
+                          gp_stats *stats, const gp_tuning *t);
+gp_status run_locator(const gp_grid *g, int64_t n, const double *px, const double *py,
+                      int32_t *out_id, double *out_dist, gp_precision prec, const Workspace &w,
+                      hipStream_t s, gp_stats *stats, bool count);
 }  // namespace gp
 
 using namespace gp;
@@ -94,6 +99,10 @@ struct Request {
   gp_status status = GP_OK;
 };
 
+// How a chunk runs: the tiled refinement or the locator on the block's copies, or the locator on
+// the request's own buffers.
+enum class Path { kTiled, kBlock, kInPlace };
+
 // Device buffers of one chunk, carved from the arena: inputs, outputs, workspace.
 struct Block {
   size_t off = 0, bytes = 0;
@@ -104,7 +113,7 @@ struct Block {
   void *ws = nullptr;
   size_t ws_bytes = 0;
   hipGraphExec_t graph = nullptr;
-  bool graph_locator = false;  // captured on the locator's path, which the grid's tuning decides
+  Path graph_path = Path::kTiled;  // of `graph`
   uint64_t last_use = 0;
 };
 
@@ -256,10 +265,10 @@ static Block *acquire_block(gp_server *srv, gp_kind kind, int64_t b) {
       return set_error(GP_E_HIP, "%s failed: %s", #expr, hipGetErrorString(e_));         \
   } while (0)
 
-// Forget an idle block's graph when it was captured on the other of the two paths (the
-// grid's tuning has changed since).
-static void drop_graph_of_path(Block *blk, bool other) {
-  if (!blk->graph || !other) return;
+// Forget a block's graph when it was captured on another path than the chunk's (the grid's
+// tuning has changed since, or the last request's results lay over its points).
+static void keep_graph_of(Block *blk, Path path) {
+  if (!blk->graph || blk->graph_path == path) return;
   (void)hipGraphExecDestroy(blk->graph);
   blk->graph = nullptr;
 }
@@ -274,10 +283,16 @@ static gp_status enqueue_chunk(gp_server *srv, Lane &ln, Request *r, Block *blk,
   const gp_grid *g = srv->grid[r->kind];
   const int64_t b = blk->bucket;
   const gp_precision prec = (gp_precision)o.precision;
-  // (of the whole request: a chunk's results may lie over another chunk's points)
-  if (o.inputs_on_device && uses_locator(*(const Grid *)g, prec) &&
-      !results_over_points(r->n, r->px, r->py, r->out_id,
-                           r->kind == GP_P2P ? r->out_dist : nullptr, true)) {
+  // the chunk's path, decided once: the grid's tuning may change meanwhile.  Overlap is that of
+  // the whole request: a chunk's results may lie over another chunk's points.
+  const Path path = !uses_locator(*(const Grid *)g, prec) ? Path::kTiled
+                    : o.inputs_on_device &&
+                            !results_over_points(r->n, r->px, r->py, r->out_id,
+                                                 r->kind == GP_P2P ? r->out_dist : nullptr, true)
+                        ? Path::kInPlace
+                        : Path::kBlock;
+  if (o.use_graphs) keep_graph_of(blk, path);
+  if (path == Path::kInPlace) {
     // The locator needs no workspace and no order of the points: it runs on the request's own
     // buffers.  A chunk is handed over through the block's memory, so the captured query
     // replays for any buffers and sizes of its bucket.
@@ -288,7 +303,6 @@ static gp_status enqueue_chunk(gp_server *srv, Lane &ln, Request *r, Block *blk,
                                              r->out_dist ? r->out_dist + lo : nullptr, m,
                                              ln.h_tests}, s));
     if (o.use_graphs) {
-      drop_graph_of_path(blk, !blk->graph_locator);
       if (!blk->graph) {
         hipGraph_t graph;
         SV_TRY(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
@@ -301,7 +315,7 @@ static gp_status enqueue_chunk(gp_server *srv, Lane &ln, Request *r, Block *blk,
         (void)hipGraphDestroy(graph);
         SV_TRY(ei);
         blk->graph = exec;
-        blk->graph_locator = true;
+        blk->graph_path = path;
       }
       SV_TRY(hipGraphLaunch(blk->graph, s));
       std::lock_guard<std::mutex> lk(srv->mu);
@@ -333,15 +347,17 @@ static gp_status enqueue_chunk(gp_server *srv, Lane &ln, Request *r, Block *blk,
   // vertex-parallel (lanes over edges or segments) instead of leaving most lanes idle
   if (tn.vp_points < 0 && (double)b < 4.0 * (double)((const Grid *)g)->ncells)
     tn.vp_points = 4;
-  // a grid at the library default runs its chunks on the locator
-  const gp_tuning *tp = uses_locator(*(const Grid *)g, prec) ? nullptr : &tn;
+  auto query = [&]() {
+    if (path == Path::kBlock)
+      return run_locator(g, nq, blk->px, blk->py, blk->id, blk->dist, prec, w, s, nullptr, true);
+    return run_query_tuned(g, r->kind, nq, blk->px, blk->py, blk->id, blk->dist, prec, blk->ws,
+                           blk->ws_bytes, s, nullptr, &tn);
+  };
   if (o.use_graphs) {
-    drop_graph_of_path(blk, blk->graph_locator);
     if (!blk->graph) {
       hipGraph_t graph;
       SV_TRY(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
-      gp_status rc = run_query_tuned(g, r->kind, b, blk->px, blk->py, blk->id, blk->dist, prec,
-                                     blk->ws, blk->ws_bytes, s, nullptr, tp, true);
+      gp_status rc = query();
       hipError_t ec = hipStreamEndCapture(s, &graph);
       if (rc) return rc;
       SV_TRY(ec);
@@ -350,14 +366,13 @@ static gp_status enqueue_chunk(gp_server *srv, Lane &ln, Request *r, Block *blk,
       (void)hipGraphDestroy(graph);
       SV_TRY(ei);
       blk->graph = exec;
-      blk->graph_locator = false;
+      blk->graph_path = path;
     }
     SV_TRY(hipGraphLaunch(blk->graph, s));
     std::lock_guard<std::mutex> lk(srv->mu);
     srv->replays++;
   } else {
-    gp_status rc = run_query_tuned(g, r->kind, m, blk->px, blk->py, blk->id, blk->dist, prec,
-                                   blk->ws, blk->ws_bytes, s, nullptr, tp, true);
+    gp_status rc = query();
     if (rc) return rc;
   }
   SV_TRY(hipMemcpyAsync(r->out_id + lo, blk->id, (size_t)m * 4, out_kind, s));

@@ -229,3 +229,49 @@ def test_results_over_the_points(gp, kind):
             for key in ("n_points", "n_paired", "tests"):
                 assert st[key] == want_st[key], key
     srv.close()
+
+
+def circle(n):
+    t = np.arange(n) * (2 * np.pi / n)
+    return 0.5 + 0.45 * np.cos(t), 0.5 + 0.45 * np.sin(t)
+
+
+def test_served_host_chunks_follow_the_tuning(gp):
+    """Chunks of host memory, captured graphs replayed: after gp_set_tuning a request runs
+    the tiled refinement, after gp_reset_tuning the locator again.  The paths' results are
+    the same bits, so the time tells them apart: 65,536 points against a ring of 100,000
+    edges in every cell are 6.5e9 FP64 tests on the one and a few reads a point on the
+    other."""
+    m, n = 100_000, 65_536
+    x, y = circle(m)
+    geom = synth.Geometry("pip", np.array([0, m]), x, y, np.array([0, 1]))
+    params = synth.GridParams(cell_size=0.25, x0=0.0, y0=0.0, nx=4, ny=4)
+    grid = gp.gp_build_grid("pip", geom, params)
+    px, py = np.random.default_rng(9).uniform(0, 1, (2, n))
+    hx, hy = (torch.from_numpy(v).pin_memory() for v in (px, py))
+    r = np.hypot(px - 0.5, py - 0.5)
+    sure = np.abs(r - 0.45) > 1e-6
+    srv = gp.Server(grid, None, n_slots=1, slot_points=n, mem_budget=1 << 30, precision="fp64",
+                    inputs_on_device=False)
+    out = torch.empty(n, dtype=torch.int32).pin_memory()
+
+    def best():
+        times = []
+        for _ in range(4):
+            out.fill_(-9)
+            t0 = time.perf_counter()
+            srv.wait(srv.submit("pip", hx, hy, out))
+            times.append(time.perf_counter() - t0)
+            assert np.array_equal(out.numpy()[sure], np.where(r < 0.45, 0, -1)[sure])
+        return min(times)
+
+    default, times = gp.gp_get_tuning(grid, "fp64"), []
+    for tiled in (False, True, False, True):
+        if tiled:
+            gp.gp_set_tuning(grid, "fp64", **default)
+        else:
+            gp.gp_reset_tuning(grid, "fp64")
+        times.append(best())
+    srv.close()
+    print("ms", [round(1e3 * t, 3) for t in times], flush=True)
+    assert min(times[1], times[3]) > 4 * max(times[0], times[2]), times
