@@ -1114,21 +1114,29 @@ static gp_status keep_tuning(gp_grid *g, gp_precision prec, int64_t n, const dou
                              const double *py, int32_t *id, double *dist, void *ws,
                              size_t ws_bytes, hipStream_t s, const gp_tuning &cfg, float ms,
                              float *best_ms) {
+  const gp_tuning old = g->tune[prec];
+  const bool old_explicit = g->tune_explicit[prec];
   g->tune[prec] = cfg;
   g->tune_explicit[prec] = false;
   float best = ms;
+  bool tiled = true;
   if (uses_locator(*g, prec)) {
     float times[3];
     for (int r = 0; r < 4; ++r) {
       gp_stats st;
       gp_status rc = run_query(g, g->kind, n, px, py, id, dist, prec, ws, ws_bytes, s, &st, nullptr);
-      if (rc) return rc;
+      if (rc) {
+        g->tune[prec] = old;
+        g->tune_explicit[prec] = old_explicit;
+        return rc;
+      }
       if (r > 0) times[r - 1] = st.ms_total;
     }
     std::sort(times, times + 3);
     best = std::min(ms, times[1]);
+    tiled = !locator_kept(times[1], ms);
   }
-  g->tune_explicit[prec] = best >= ms;
+  g->tune_explicit[prec] = tiled;
   if (best_ms) *best_ms = best;
   return GP_OK;
 }

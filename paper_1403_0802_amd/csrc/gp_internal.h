@@ -161,9 +161,14 @@ struct Grid {
   LocSeg *d_loc_seg;
   int64_t loc_bytes;
   gp_tuning tune[2];
-  bool tune_explicit[2];  // tune[prec] was set by gp_set_tuning or gp_autotune
+  bool tune_explicit[2];  // queries run tune[prec]: set by gp_set_tuning, or by gp_autotune
+                          // where the locator was not at least as fast
   int num_cu;
 };
+
+// Whether the autotuner leaves a grid's queries on its locator, from the times of a sample on
+// the locator and on the fastest configuration of the tiled refinement.
+inline bool locator_kept(float ms_locator, float ms_tiled) { return ms_locator <= ms_tiled; }
 
 // What the locator's queries read; a cell's subcells are numbered row by row.
 struct LocArgs {
