@@ -3,7 +3,8 @@
 One step is one query batch through the whole per-batch path (cell hash, stable sort,
 gather/rebase, work items, refinement, FP64 recheck, output) for BOTH operations:
   PIP  configuration 3: 50M points against 5,000 Voronoi polygons (holes, up to
-       50,000 vertices), grid 512 x 512 of 1/512 cells (the fastest of the cell-size sweep);
+       50,000 vertices), grid 512 x 512 of 1/512 cells (within 3% of the
+       fastest of the cell-size sweep);
   P2P  configuration 4: 200M points against 200,000 random-walk polylines, D = 100 m,
        grid 400 x 400 of 100 m cells;
 in the mixed-precision form, on the tiled refinement, which performs every candidate test
@@ -106,8 +107,8 @@ def write_traffic(fetch_csv: str, write_csv: str):
 
 
 WORKLOAD_NAME = "C3 PIP 50M pts x 5000 polygons + C4 P2P 200M pts x 200000 polylines, mixed"
-# The grids of the step (the full-size parity tests build the same ones).  PIP: 1/512, the
-# fastest PIP query of the cell-size sweep (bench.py --cell-sweep), with build-time
+# The grids of the step (the full-size parity tests build the same ones).  PIP: 1/512, within
+# 3% of the fastest PIP query of the cell-size sweep (bench.py --cell-sweep), with build-time
 # per-(cell, polygon) edge records (prestage).  P2P: 100 m cells with
 # build-time segment records (prestage), an index structure like the candidate lists;
 # detail.p2p_plain_grid runs the grid without them.
@@ -348,7 +349,10 @@ def serving_run(gp, torch, grid3, grid4, pools, n_requests: int, n_warmup: int, 
 def cell_sweep(gp, torch, dev, c3, c4, which="both"):
     """The filter-versus-refine trade-off (Sec. III.A): query time, candidate pairs, tests
     and grid memory at five cell sizes around each configuration's default, on the full
-    point sets, mixed form, default kernel tuning; `which` is "pip", "p2p" or "both"."""
+    point sets, mixed form; `which` is "pip", "p2p" or "both".  `ms` is the tiled refinement's
+    (the headline's path, in its default configuration with an untuned grid's rule for few
+    points per cell), `ms_locator` that of the library's default path; the best size is the
+    tiled refinement's."""
     out = {}
     for name, kind, (geom, p, px, py), sizes in (
             ("pip_c3", "pip", c3, [1 / 128, 1 / 256, 1 / 512, 1 / 1024, 1 / 2048]),
@@ -361,7 +365,28 @@ def cell_sweep(gp, torch, dev, c3, c4, which="both"):
             p = dataclasses.replace(p, prestage=0)
         x, y = torch.from_numpy(px).to(dev), torch.from_numpy(py).to(dev)
         t0 = time.perf_counter()
-        best, rows = gp.gp_sweep_cell_size(kind, geom, p, sizes, x, y, "mixed")
+        rows = []
+        for cs in sizes:
+            f = p.cell_size / cs
+            grid = gp.gp_build_grid(kind, geom, dataclasses.replace(
+                p, cell_size=cs, nx=math.ceil(p.nx * f), ny=math.ceil(p.ny * f)))
+            info = grid.info()
+            ws = gp.new_workspace(grid, len(px), "mixed", dev)
+
+            def median_ms():
+                runs = [gp.run(grid, x, y, "mixed", ws=ws, stats=True)[-1] for _ in range(4)]
+                return sorted(r["ms_total"] for r in runs[1:])[1], runs[-1]["tests"]
+            ms_locator, tests = median_ms()
+            t = gp.gp_get_tuning(grid, "mixed")
+            if len(px) < 256 * info["nx"] * info["ny"]:
+                t["points_per_lane"] = min(t["points_per_lane"], 2)
+            gp.gp_set_tuning(grid, "mixed", **t)
+            ms, _ = median_ms()
+            rows.append({"cell_size": cs, "ms": ms, "ms_locator": ms_locator,
+                         "pairs": info["n_pairs"], "tests": tests,
+                         "grid_bytes": info["device_bytes"]})
+            del grid, ws
+        best = min(rows, key=lambda r: r["ms"])["cell_size"]
         log(f"[bench] {name} sweep {time.perf_counter() - t0:.1f}s best {best}")
         out[name] = {"default_cell_size": p.cell_size, "best_cell_size": best, "rows": rows}
         del x, y
@@ -394,7 +419,8 @@ def main():
                     help="first run one plain 1 GiB device copy (counter calibration)")
     ap.add_argument("--cell-sweep", nargs="?", const="both", choices=("pip", "p2p", "both"),
                     help="instead of the step: sweep the cell size of both grids on the full "
-                         "workloads (gp_sweep_cell_size) and print one JSON line")
+                         "workloads, on the headline's path and on the default one, and "
+                         "print one JSON line")
     ap.add_argument("--traffic-from", nargs=2, metavar=("FETCH_CSV", "WRITE_CSV"),
                     help="write profiles/traffic.json from two rocprofv3 --pmc counter "
                          "CSVs of a --copy-probe run, then exit")
@@ -714,9 +740,10 @@ def main():
                    "p2p_polylines": geom4.n_features, "radius_D_m": 100.0,
                    "pip_grid": {"cell_size": p3.cell_size, "nx": p3.nx, "ny": p3.ny,
                                 "prestage": int(getattr(p3, "prestage", 0)),
-                                "note": "1/512 cells, the fastest PIP query of the cell-size "
-                                        "sweep (the survey's C3 grid is 1/1024), with "
-                                        "build-time per-(cell, polygon) edge records"},
+                                "note": "1/512 cells, within 3% of the fastest PIP query of "
+                                        "the cell-size sweep (the survey's C3 grid is "
+                                        "1/1024), with build-time per-(cell, polygon) edge "
+                                        "records"},
                    "p2p_grid": {"cell_size_m": p4.cell_size, "nx": p4.nx, "ny": p4.ny,
                                 "prestage": int(getattr(p4, "prestage", 0)),
                                 "note": "with build-time per-(cell, segment) FP32 records"},
