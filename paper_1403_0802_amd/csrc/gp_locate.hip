@@ -46,6 +46,11 @@ __device__ __forceinline__ void wave_lds_sync() {
   __builtin_amdgcn_wave_barrier();
 }
 
+// *p = max(*p, v): an atomic only where the value seen is smaller.
+__device__ __forceinline__ void raise_to(unsigned long long *p, unsigned long long v) {
+  if (v > __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(p, v);
+}
+
 unsigned blocks_for(int64_t n, int64_t per, int64_t cap) {
   return (unsigned)std::max<int64_t>(1, std::min<int64_t>((n + per - 1) / per, cap));
 }
@@ -263,7 +268,7 @@ __global__ __launch_bounds__(256) void k_loc_pip_cells(const int32_t *cand_off,
     atomicAdd(cost, s0);
     atomicAdd(cost + 1, s1);
     atomicAdd(cost + 2, s2);
-    atomicMax(cost + 3, most);
+    raise_to(cost + 3, most);
   }
 }
 
@@ -591,7 +596,7 @@ __global__ __launch_bounds__(256) void k_loc_p2p_cells(const uint32_t *first, co
     atomicAdd(cost + 1, s1);
     atomicAdd(cost + 2, s2);
     atomicAdd(cost + 3, s3);
-    atomicMax(cost + 4, most);
+    raise_to(cost + 4, most);
   }
 }
 
@@ -1398,15 +1403,10 @@ hipError_t scan_counts(uint32_t *cnt, size_t n, int64_t most, unsigned long long
   return launch_exclusive_scan_u32(cnt, cnt, n + 1, tmp, s);
 }
 
-// Whether the first passes stay within their limits.
-hipError_t work_fits(const Grid &g, unsigned long long *sum, bool *fits, hipStream_t s) {
-  unsigned long long work[2] = {0, 0};
-  LOC_TRY(launch_fill_u32((uint32_t *)sum, 0u, 4, s));
-  LOC_TRY(launch_loc_work(g, sum, s));
-  LOC_TRY(read_back(work, sum, 16, s));
-  *fits = work[0] <= (unsigned long long)kMaxPairEdges &&
-          work[1] <= (unsigned long long)kMaxCellEdges;
-  return hipSuccess;
+// Whether the first passes stay within their limits, from k_loc_work's sums.
+bool work_fits(const unsigned long long *work) {
+  return work[0] <= (unsigned long long)kMaxPairEdges &&
+         work[1] <= (unsigned long long)kMaxCellEdges;
 }
 
 hipError_t build_pip(Grid &g, const LocBuild &b, double pad, hipStream_t s) {
@@ -1423,9 +1423,11 @@ hipError_t build_pip(Grid &g, const LocBuild &b, double pad, hipStream_t s) {
   uint8_t *par = b1.as<uint8_t>(o_par);
   unsigned long long *sum = b1.as<unsigned long long>(o_sum);
   LocCell *cell = cells.as<LocCell>();
-  bool fits = false;
-  LOC_TRY(work_fits(g, sum, &fits, s));
-  LOC_NEED(fits);
+  unsigned long long work[2] = {0, 0};
+  LOC_TRY(launch_fill_u32((uint32_t *)sum, 0u, 4, s));
+  LOC_TRY(launch_loc_work(g, sum, s));
+  LOC_TRY(read_back(work, sum, 16, s));
+  LOC_NEED(work_fits(work));
   int64_t total = 0;
   LOC_TRY(launch_loc_ring_prev(b.ring_off, b.n_rings, prev, s));
   if (np) LOC_TRY(launch_loc_pip_pairs(g, b.pair_cell, b.vy, prev, pad, cnt, par, nullptr, s));
@@ -1489,20 +1491,18 @@ hipError_t build_p2p(Grid &g, double pad, double slack, hipStream_t s) {
   unsigned long long *sum = b1.as<unsigned long long>(o_sum);
   int32_t *place = b1.as<int32_t>(o_place);
   LocSegCell *cell = cells.as<LocSegCell>();
-  bool fits = false;
-  LOC_TRY(work_fits(g, sum, &fits, s));
-  LOC_NEED(fits);
+  unsigned long long work[3] = {0, 0, 0};  // and whether a segment is too short (kMinLen2)
+  LOC_TRY(launch_fill_u32((uint32_t *)sum, 0u, 6, s));
+  LOC_TRY(launch_loc_work(g, sum, s));
+  if (nseg)
+    LOC_TRY(launch_loc_seg_keys(g, kMinLen2 * std::max(1.0, 1.0 / (g.cs * g.cs)),
+                                b1.as<uint32_t>(o_kA), (uint32_t *)(sum + 2), s));
+  LOC_TRY(read_back(work, sum, 24, s));
+  LOC_NEED(work_fits(work) && !work[2]);
   if (nseg) {  // the segments in the order of the cells
     uint32_t *keys = nullptr, *order = nullptr;
     int bits = 1;
     while (bits < 31 && (1 << bits) < g.ncells) ++bits;
-    // a segment too short for its cross products (kMinLen2): the grid goes without
-    uint32_t tiny = 0;
-    LOC_TRY(launch_fill_u32((uint32_t *)sum, 0u, 1, s));
-    LOC_TRY(launch_loc_seg_keys(g, kMinLen2 * std::max(1.0, 1.0 / (g.cs * g.cs)),
-                                b1.as<uint32_t>(o_kA), (uint32_t *)sum, s));
-    LOC_TRY(read_back(&tiny, sum, 4, s));
-    LOC_NEED(!tiny);
     LOC_TRY(launch_loc_polylines(g, b1.as<int32_t>(o_poly), s));
     LOC_TRY(launch_radix_sort(b1.as<uint32_t>(o_kA), b1.as<uint32_t>(o_kB),
                               b1.as<uint32_t>(o_vA), b1.as<uint32_t>(o_vB), nseg, bits, true,
