@@ -1324,8 +1324,14 @@ hipError_t launch_locate_count(const LocArgs &a, const double *px, const double 
 namespace {
 
 // Limits of the index: slots of 32 bytes (PIP), subcells of a 128-byte line each, expected
-// entries and further blocks (P2P), tests of the build, and entries per subcell beyond which the tiled refinement, which
-// reads a list once for 64 and more points, is the better reader of it.
+// entries and further blocks (P2P), tests of the build, and entries per subcell.  The last line
+// is drawn for P2P lists that no query can stop early, all of whose segments are equally far
+// (points anywhere in the box of a circle of m edges, 2M of them, locator against tiled
+// refinement, FP64): m = 400, 35 entries a subcell, 0.55 against 1.29 ms (near the centre, 400
+// entries, 1.81 against 1.58); m = 4000, 400 entries, 6.1 against 5.8 ms (17.4 against 7.5).
+// Other lists stay the better path far beyond it (short segments at random: 131 entries 0.14
+// against 59 ms; PIP, spikes that cross the cell: 113 entries 2.7 against 8.8 ms, 1812 entries
+// 49 against 121 ms), where the index grows by 32 bytes an entry (PIP).
 constexpr int64_t kMaxSlots = int64_t(1) << 27;     // 4 GiB
 constexpr int64_t kMaxEntries = int64_t(1) << 29;
 constexpr int64_t kMaxLines = int64_t(1) << 25;     // 4 GiB
