@@ -275,3 +275,54 @@ def test_served_host_chunks_follow_the_tuning(gp):
     srv.close()
     print("ms", [round(1e3 * t, 3) for t in times], flush=True)
     assert min(times[1], times[3]) > 4 * max(times[0], times[2]), times
+
+
+@pytest.mark.parametrize("kind,at,has", [("pip", 2.0 ** 30, True), ("pip", 2.0 ** 42, None),
+                                         ("pip", 2.0 ** 60, None), ("pip", 1e151, False),
+                                         ("p2p", 2.0 ** 27, True), ("p2p", 2.0 ** 29, False)])
+def test_outlying_feature(gp, kind, at, has):
+    """One feature ``at`` cell sizes away: the build's pads grow with it, past a cell and past
+    the grid, until the grid goes without a locator."""
+    w = (synth.config1(n_points=20_000, grid_n=4, seed_salt=2) if kind == "pip"
+         else synth.config2(n_points=20_000, n_lines=1_000, seed_salt=2))
+    g, at = w.geom, at * w.params.cell_size
+    geom = synth.Geometry(kind, np.append(g.ring_vert_off, len(g.x) + 3),
+                          np.append(g.x, at * np.array([1.0, 1.25, 1.0])),
+                          np.append(g.y, at * np.array([1.0, 1.0, 1.25])),
+                          None if kind == "p2p" else np.append(g.feature_ring_off,
+                                                               len(g.ring_vert_off)))
+    og = oracle.build_grid(geom, w.params)
+    want = (oracle.pip(geom, w.px, w.py, og),) if kind == "pip" else oracle.p2p(
+        geom, w.px, w.py, w.params.radius_D, og)
+    grid = gp.gp_build_grid(kind, geom, w.params)
+    got = gp.run(grid, *dev(w.px, w.py), "fp64", stats=True)
+    print(kind, at, "locator" if on_locator(got[-1]) else "tiled", flush=True)
+    assert has is None or on_locator(got[-1]) == has
+    for a, b in zip(got, want):
+        assert np.array_equal(a.cpu().numpy(), b)
+
+
+@pytest.mark.parametrize("config", ["stars", "regions", "walks", "roads"])
+def test_the_configurations_have_a_locator(gp, config):
+    """The feature sets and cells of the configurations, with every option: queries at the
+    library default take the locator, an explicit tuning the tiled refinement."""
+    if config == "stars":
+        w = synth.config1(n_points=2_000)
+        kind, geom, params, pts = "pip", w.geom, w.params, (w.px, w.py)
+    elif config == "walks":
+        w = synth.config2(n_points=2_000)
+        kind, geom, params, pts = "p2p", w.geom, w.params, (w.px, w.py)
+    elif config == "regions":
+        kind, geom, pts = "pip", synth.config3_geometry()[0], synth.config3_points(2_000)
+        params = synth.GridParams(cell_size=1 / 512, nx=512, ny=512)
+    else:
+        kind, geom, pts = "p2p", synth.config4_geometry(), synth.config4_points(2_000)
+        params = synth.GridParams(cell_size=100.0, radius_D=100.0, nx=400, ny=400)
+    x, y = dev(*pts)
+    lists = "cell_classes" if kind == "pip" else "segment_filter"
+    for options in ({}, {"prestage": 1}, {lists: 1}, {"prestage": 1, lists: 1}):
+        grid = gp.gp_build_grid(kind, geom, synth.GridParams(**{**params.__dict__, **options}))
+        for prec in ("fp64", "mixed"):
+            assert on_locator(gp.run(grid, x, y, prec, stats=True)[-1]), (config, options, prec)
+            gp.gp_set_tuning(grid, prec, **gp.gp_get_tuning(grid, prec))
+            assert not on_locator(gp.run(grid, x, y, prec, stats=True)[-1])
