@@ -31,13 +31,17 @@
  *     no such polyline, id -1 and distance +inf.
  *
  * Precision forms:
- *   GP_FP64  every test in FP64 with exactly the operation order above (results are
- *            bitwise reproducible against a scalar FP64 implementation).
- *   GP_MIXED tests in FP32 on coordinates rebased to each grid cell's centre, with a
- *            per-edge guard band; any point whose FP32 decision could differ from the
- *            FP64 one is recomputed in FP64 on the GPU.  PIP ids, P2P ids and P2P
- *            distances are identical to GP_FP64: the winning polylines' distances are
- *            always evaluated in FP64, in the operation order above.
+ *   GP_FP64  results decided in FP64 with exactly the operation order above (bitwise
+ *            reproducible against a scalar FP64 implementation).
+ *   GP_MIXED may test in FP32; any point whose FP32 decision could differ from the FP64
+ *            one is decided in FP64 on the GPU.  PIP ids, P2P ids and P2P distances are
+ *            identical to GP_FP64: the winning polylines' distances are always evaluated
+ *            in FP64, in the operation order above.
+ *   On the tiled refinement (see gp_grid) GP_FP64 performs every test in FP64, GP_MIXED in
+ *   FP32 on coordinates rebased to each cell's centre, with a guard band per edge.  On the
+ *   locator both forms are the same: what the grid's index leaves for a point is decided in
+ *   FP64, PIP by the crossing test, P2P by the distances of those segments that FP32
+ *   distances on 16-bit endpoints, with a bound on their error, cannot rule out.
  *
  * Conventions:
  *   - All calls return a gp_status; 0 is success.  gp_last_error() returns a
@@ -101,18 +105,18 @@ typedef struct gp_geometry {
  * build time (Sec. III.A): a pair whose cell, widened by max(cs*2^-20, M*2^-40) with M
  * the largest grid coordinate magnitude, meets no edge's bounding box lies wholly
  * inside or wholly outside the polygon, decided by the FP64 crossing parity of the cell
- * centre; every other pair is a boundary pair.  Queries then skip outside pairs, give
- * every still undecided point of the cell an inside pair's id without testing, and test
- * only boundary pairs.  Results are identical to the unclassified grid; gp_stats.tests
- * counts the tests performed and tests_avoided the candidate tests skipped.
+ * centre; every other pair is a boundary pair.  The tiled refinement then skips outside
+ * pairs, gives every still undecided point of the cell an inside pair's id without testing,
+ * and tests only boundary pairs.  Results are identical to the unclassified grid;
+ * gp_stats.tests counts the tests of the boundary pairs and tests_avoided the others.
  * p2p_segment_filter = 1 (P2P only; 0 otherwise) also rasterises every segment's
  * bounding box, expanded by D and padded like the MBBs, and keeps per cell the list of
- * segments it reaches; the GP_MIXED form then tests only those (a segment farther than
+ * segments it reaches; the tiled GP_MIXED form then tests only those (a segment farther than
  * D from the whole cell can neither be a point's nearest segment within range nor bring
  * a polyline into range), with the same results; tests and tests_avoided as above.  The
  * GP_FP64 form keeps testing every candidate segment.
  * prestage = 1 (0 otherwise) computes at build time, for every cell, the cell-relative
- * FP32 records of the GP_MIXED form, which its queries then read instead of computing
+ * FP32 records of the tiled GP_MIXED form, which its queries then read instead of computing
  * them per work item; same results.  P2P (ignored with p2p_segment_filter): the records
  * of all the cell's candidate segments and the cell's error bounds, 20 bytes per (cell,
  * candidate segment).  PIP: per (cell, candidate polygon) pair its edges' records in
@@ -120,7 +124,9 @@ typedef struct gp_geometry {
  * point of the cell, edges right of the cell whose crossing reduces to the half-open
  * straddle of the point's y (with a flag for a point level with an endpoint in FP32), and
  * guarded edges near the cell (test plus error-band flag) -- 16 bytes per edge (32 per
- * guarded edge).  Reported in gp_grid_info.device_bytes. */
+ * guarded edge).  Reported in gp_grid_info.device_bytes.
+ * The three options serve the tiled refinement: queries on a grid's locator read none of
+ * what they add (the counters above apart). */
 typedef struct gp_grid_params {
     double cell_size;
     double radius_D;
@@ -135,11 +141,19 @@ typedef struct gp_grid gp_grid;
 
 /* Queries run on one of two paths, with the same results.  A grid carries a locator, a
  * per-point index built with it (subcells with only the edges or segments that can decide
- * a point there), unless its size, its cells against its coordinates (P2P: 2^28 and more
- * cell sizes from the origin) or the device's memory forbid one; queries use it while the
- * grid is at the library default.  An explicit gp_tuning, and every grid without a
- * locator, runs the tiled refinement: points sorted by cell, every candidate test of a
- * cell's points performed by a work item. */
+ * a point there), and queries use it while the grid is at the library default.  An explicit
+ * gp_tuning, a query whose results overlap its points in memory (distances exactly over x or
+ * y apart, unless stats are asked for), and every grid without a locator run the tiled
+ * refinement: points sorted by cell, every candidate test of a cell's points performed by a
+ * work item.
+ * A grid goes without a locator above 2^26 cells; with coordinates of 1e150 and more or
+ * cells of 1e-140 and less; for P2P also with coordinates of 2^28 cell sizes or 2^250 and
+ * more, or with a segment, other than a point, of squared length below 2^-900 or
+ * 2^-900 / cell_size^2 (where the definition's FP64 squares over- or underflow); when its
+ * candidates hold more than 2^36 edges over all cells or 2^22 in one (the build's work), or
+ * its lists more than fixed sizes (4 to 8 GiB a part, 2^20 entries in a cell, 64 a subcell on
+ * average); and where the device memory left after everything else of the grid does not
+ * hold it.  It costs build time and memory (gp_grid_info.device_bytes includes it). */
 
 /* Configuration of the tiled refinement chosen by gp_autotune or set by hand (0 = library
  * default). */
@@ -249,13 +263,16 @@ gp_status gp_query_noalloc(const gp_grid *grid, gp_kind kind, int64_t n, const d
 
 /* Kernel configuration of a grid for one precision form.  gp_set_tuning selects the tiled
  * refinement with that configuration; with a NULL tuning it restores the library default
- * (the locator, where the grid has one). */
+ * (the locator, where the grid has one).  gp_get_tuning gives the tiled refinement's
+ * configuration whichever path queries take, so setting what it gave selects that path. */
 gp_status gp_set_tuning(gp_grid *grid, gp_precision prec, const gp_tuning *tuning);
 gp_status gp_get_tuning(const gp_grid *grid, gp_precision prec, gp_tuning *tuning);
 
 /* Autotuner: times every configuration of a built-in search space on the given
  * (device) sample points, keeps the fastest, stores it in the grid and returns it; queries
- * stay on the grid's locator where that is at least as fast (*best_ms is the faster time).
+ * stay on the grid's locator where that is at least as fast (*best_ms is the faster time;
+ * *best is the tiled refinement's fastest configuration either way, and setting it later
+ * with gp_set_tuning leaves the locator).
  * Results never depend on the configuration.  The winner is cached in the process by
  * (operation, precision, GPU architecture, the grid's build-time options, workload class:
  * the octaves of the sample size, of the tests per paired point and of the paired points
@@ -281,8 +298,8 @@ gp_status gp_tuning_cache_size(int64_t *entries);
  * area: nx = ceil(nx0 * cs0 / cs)), runs the query on the n sample points (device
  * pointers) once to warm up and three times timed, and frees the grid again.  Per size
  * i: ms_query[i] the median gp_stats.ms_total (NAN when that grid exceeds the library's
- * limits), n_pairs[i] the candidate pairs, tests[i] the tests performed, grid_bytes[i]
- * the grid's device memory.  *best receives the fastest size.  Any per-size output may
+ * limits), n_pairs[i] the candidate pairs, tests[i] gp_stats.tests, grid_bytes[i] the
+ * grid's device memory; queries run at the library default.  *best receives the fastest size.  Any per-size output may
  * be NULL.  Results never depend on the cell size.  Allocates; synchronous. */
 gp_status gp_sweep_cell_size(gp_kind kind, const gp_geometry *geom, const gp_grid_params *params,
                              const double *cell_sizes, int32_t n_sizes, int64_t n,
@@ -314,7 +331,9 @@ gp_status gp_probe_rate(int32_t which, int32_t iters, double *rate, float *ms);
  * block fits in the arena: the chunks of a large request spread over the free streams,
  * and requests that arrive while others run start as streams and memory free up, so
  * their work overlaps on the device.  Each block captures its query into a hipGraph at
- * first use and replays it (use_graphs = 1). */
+ * first use and replays it (use_graphs = 1).  A chunk with device inputs on a grid's locator
+ * reads and writes the request's own buffers; its block, of the same size, then holds only
+ * the hand-over. */
 typedef struct gp_serve_opts {
     int32_t n_slots;          /* chunks running at once (one HIP stream each), 1..16 */
     int64_t slot_points;      /* largest chunk, in points, in [1024, 2^30) */

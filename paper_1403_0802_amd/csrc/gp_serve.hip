@@ -16,11 +16,12 @@
 // over all free streams, and requests that arrive while others are on the GPU start as
 // soon as a stream and memory free up, so their work overlaps on the device.
 //
-// Locator.  Where the grid's queries run on its locator and inputs are on the device, a chunk
-// reads the request's points and writes its results in place: the two input copies, the NaN
+// Locator.  Where the grid's queries run on its locator, inputs are on the device and the
+// request's results do not lie over its points, a chunk reads the request's points and writes
+// its results in place: the two input copies, the NaN
 // tail, the output copies and the count's copy to the host are gone, and the block's memory
 // holds the hand-over of the request to the captured query (16 requests of 1K-4M points in a
-// burst: 1277 -> 663 us).
+// burst: 1277 -> 650 to 720 us).
 //
 // Graphs.  A block captures its query pipeline into a hipGraph the first time it runs
 // and replays it for every later chunk of its shape.  Buckets are powers of two from

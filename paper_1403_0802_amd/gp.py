@@ -226,7 +226,8 @@ def gp_build_grid(kind, geom, params, stream=None) -> Grid:
     classifies every cell/polygon pair at build time), ``segment_filter`` (P2P: 1 keeps
     per cell only the segments within D of it, for the mixed form) and ``prestage`` (1
     computes every cell's mixed-form records at build time: P2P segment records, PIP
-    per (cell, polygon) edge records)."""
+    per (cell, polygon) edge records); the three serve the tiled refinement, which an
+    explicit tuning selects."""
     k = KINDS.get(kind, kind)
     g, keep = _geometry(geom)
     p = _params(params)
